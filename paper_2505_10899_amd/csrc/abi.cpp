@@ -12,6 +12,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/vclb.h"
@@ -153,6 +154,18 @@ struct Layout {
   long partial_blocks;
 };
 
+// workgroups whose partial reductions the workspace holds: every march shape uses at least
+// 64 nodes per workgroup, plus one partial row per (y, z) line for tiles ragged in x
+long partial_blocks_for(const vclb_params& p) {
+  return long(size_t(p.nx) * p.ny * p.nz / 64) + long(p.ny) * p.nz + 64;
+}
+
+// the partial reductions of a 2D case's tiles fit the workspace (a grid of a few very long
+// rows has more tiles than that)
+bool tile2d_fits(const vclb_params& p, const vclb::Tile& t) {
+  return vclb::fused_blocks(2, p.nx, p.ny, p.nz, t) <= partial_blocks_for(p);
+}
+
 Layout layout_for(const vclb_params& p) {
   Layout L{};
   const size_t n = size_t(p.nx) * p.ny * p.nz;
@@ -174,9 +187,7 @@ Layout layout_for(const vclb_params& p) {
     }
   L.J = take(size_t(D) * ns * rb);
   for (int b = 0; b < 2; ++b) L.phis[b] = p.storage != VCLB_FP64 ? take(n * 4) : SIZE_MAX;
-  // every launch shape uses at least 64 nodes per workgroup, plus one partial row per
-  // (y, z) line for tiles that are ragged in x
-  L.partial_blocks = long(n / 64) + long(p.ny) * p.nz + 64;
+  L.partial_blocks = partial_blocks_for(p);
   for (int b = 0; b < 2; ++b) L.partials[b] = take(size_t(L.partial_blocks) * nl * 12 * sizeof(double));
   L.hist = take(size_t(vclb::kHistory) * nl * vclb::kObsFields * sizeof(double));
   L.cur = take(size_t(nl) * vclb::kObsFields * sizeof(double));
@@ -361,6 +372,35 @@ int flush_pending(vclb_case* c, hipStream_t s) {
   return rc ? fail(VCLB_EHIP, "finalize launch failed") : VCLB_OK;
 }
 
+// Whether a 2D case steps with one lane per node (tile2d.hip) or as a row march, and in
+// which tile.  Measured on square and oblong grids of 66 x 24 to 4096 x 4096, coupled and
+// vortex, each storage (us a step, march / tile):
+//  - 16 x 8 nodes and a helper wave up to 2^19 nodes, where the chain of one launch counts
+//    (512 x 256 FP32 42 / 7.1; 64 x 4 tiles 8.0);
+//  - 64 x 4 while both population sets fit the 256 MB last-level cache (777 x 1333 FP32
+//    62 / 30), 128 x 4 beyond, whose halo is a smaller share (2048 x 2048 FP64 275 / 248,
+//    2051 x 2043 FP32 227 / 161);
+//  - 4-byte arithmetic from 2^23 nodes on marches: with every CU's march long, its single
+//    read of each population beats the tiles' halos (4096 x 4096 FP32 509 / 557, FP16S
+//    352 / 361; 2944 x 2944 FP32 289 / 302), except FP32 rows that do not start on cache
+//    lines (4091 x 4096 FP32 650 / 637);
+//  - beyond 2^26 nodes the tiles' 32-bit byte offsets end (three planes of 8 bytes).
+void tile2d_choose(const vclb_params& p, vclb::Tile& t) {
+  t.lx = t.ly = 0;
+  const long n = long(p.nx) * p.ny;
+  const size_t sb = storage_bytes(p.storage);
+  const bool coupled = p.mode == VCLB_COUPLED;
+  if (n > (1L << 26)) return;
+  const bool lines = size_t(p.nx) * sb % 128 == 0;
+  if (p.storage != VCLB_FP64 && n >= (1L << 23) && !(p.storage == VCLB_FP32 && coupled && !lines)) return;
+  const size_t sets = size_t(n) * 9 * sb * (coupled ? 4 : 2);
+  vclb::Tile u = t;
+  if (n <= (1L << 19)) u.lx = 4, u.ly = 3;
+  else if (sets <= (size_t(256) << 20)) u.lx = 6, u.ly = 2;
+  else u.lx = 7, u.ly = 2;
+  if (tile2d_fits(p, u)) t = u;
+}
+
 vclb::Tile default_tile(const vclb_params& p, int ncu, bool wide_ok = true) {
   vclb::Tile t;
   if (p.lattice == VCLB_D2Q9) {
@@ -374,10 +414,15 @@ vclb::Tile default_tile(const vclb_params& p, int ncu, bool wide_ok = true) {
     t.bx = bx;
     const long strips = (p.nx + bx - 1) / bx;
     // long marches amortise the two halo rows; keep 4 waves per SIMD resident when the
-    // grid allows (1024 workgroups of up to 256 lanes, 512 of 512), with 8..64 rows each
-    long ty = (long(p.ny) * strips) / (bx > 256 ? 512 : 1024);
+    // grid allows (1024 workgroups of up to 256 lanes, 512 of 512), with 8..64 rows each.
+    // The segments of a strip are counted down, so that all workgroups are resident at
+    // once (2944 x 2944 FP32: 510 of 35 rows take 289 us, 522 of 34 rows, ten of which run
+    // alone after the others, 366).
+    const long segs = std::max(1L, (bx > 256 ? 512 : 1024) / strips);
+    const long ty = (long(p.ny) + segs - 1) / segs;
     t.ty = int(std::max(8L, std::min(64L, ty)));
     t.by3 = 1;
+    tile2d_choose(p, t);
   } else {
     // 32 x 8 columns per workgroup (a halo ring of a third of the tile, one wave per two
     // rows of 32): the fastest section measured on a 96 x 96 x 384 case.  Each workgroup
@@ -767,7 +812,7 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
   if (cache_path) {
     if (FILE* f = std::fopen(cache_path, "r")) {
       char line[4096];
-      int bx = 0, ty = 0, by3 = 0;
+      int bx = 0, ty = 0, by3 = 0, lx = 0, ly = 0;
       while (std::fgets(line, sizeof(line), f)) {
         if (!std::strstr(line, key)) continue;
         const char* pb = std::strstr(line, "\"bx\": ");
@@ -777,16 +822,38 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
           bx = std::atoi(pb + 6);
           ty = std::atoi(pt + 6);
           by3 = std::atoi(py + 7);
+          // "lane_tile": log2 of the sides of a tile of one lane per node (absent: a march)
+          const char* pl = std::strstr(line, "\"lane_tile\": [");
+          if (!pl || std::sscanf(pl + 14, "%d, %d", &lx, &ly) != 2) lx = ly = 0;
         }
       }
       std::fclose(f);
-      if (bx > 0 && ty > 0 && by3 > 0) return vclb_case_set_tile(c, bx, ty, by3);
+      if (bx > 0 && ty > 0 && by3 > 0) {
+        const int rc = vclb_case_set_tile(c, bx, ty, by3);
+        vclb::Tile t = c->tile;
+        t.lx = lx;
+        t.ly = ly;
+        if (!rc && p.lattice == VCLB_D2Q9 && vclb::tile2d_shape_ok(lx, ly) && long(p.nx) * p.ny <= (1L << 26) &&
+            tile2d_fits(p, t))
+          c->tile = t;
+        return rc;
+      }
     }
   }
   // candidates: 2D strips of bx lanes by ty rows; 3D sections of bx x by3 columns with
   // their z extent cut into as many segments as fill 1..4 workgroups per CU once
   std::vector<vclb::Tile> cands;
   if (p.lattice == VCLB_D2Q9) {
+    // where tiles of one lane per node are the default, their three shapes too; elsewhere
+    // every candidate is a march, whose results do not depend on the shape
+    const vclb::Tile def = default_tile(p, 256);
+    if (def.lx > 0)
+      for (const auto& sh : {std::pair<int, int>{4, 3}, {6, 2}, {7, 2}}) {
+        vclb::Tile t = def;
+        t.lx = sh.first;
+        t.ly = sh.second;
+        if (tile2d_fits(p, t)) cands.push_back(t);
+      }
     for (int bx : {64, 128, 256, 512, 1024}) {
       if (bx > 256 && c->p.storage == VCLB_FP64) continue;
       for (int ty : {8, 16, 32, 64, 128}) cands.push_back(vclb::Tile{bx, ty, 1});
@@ -857,8 +924,8 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
   if (cache_path) {
     if (FILE* f = std::fopen(cache_path, "a")) {
       const vclb::Tile& b = c->tile;
-      std::fprintf(f, "{\"key\": \"%s\", \"shape\": \"%s\", \"bx\": %d, \"ty\": %d, \"by3\": %d, \"ms_per_step\": %.6f, \"candidates\": [",
-                   key, desc.c_str(), b.bx, b.ty, b.by3, double(ms[size_t(best)]));
+      std::fprintf(f, "{\"key\": \"%s\", \"shape\": \"%s\", \"bx\": %d, \"ty\": %d, \"by3\": %d, \"lane_tile\": [%d, %d], \"ms_per_step\": %.6f, \"candidates\": [",
+                   key, desc.c_str(), b.bx, b.ty, b.by3, b.lx, b.ly, double(ms[size_t(best)]));
       for (size_t i = 0; i < cands.size(); ++i)
         std::fprintf(f, "%s[%d, %d, %d, %.6f]", i ? ", " : "", cands[i].bx, cands[i].ty, cands[i].by3, double(ms[i]));
       std::fprintf(f, "]}\n");

@@ -5,6 +5,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "node.hpp"
 
 namespace vclb {
@@ -194,8 +196,30 @@ __device__ __forceinline__ void accumulate(const Case& c, Acc& a, double phi, in
   }
 }
 
-// Sum nf <= 24 values over the workgroup in a fixed order (deterministic): butterfly
-// within each wave, then wave results in wave order.  Thread f < nf returns field f.
+// Sum of v over the 64 lanes of a wave in a fixed order, valid in lane 63: inclusive scans
+// of the four rows of 16 lanes, then the rows, all by data-parallel lane moves (a butterfly
+// of LDS permutes costs two permutes of about 100 cycles per step and value).  Every lane
+// of the wave must be active.
+__device__ __forceinline__ double wave_sum(double v) {
+  auto add = [&](auto ctrl, auto rows) {
+    constexpr int C = decltype(ctrl)::value, M = decltype(rows)::value;
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, int(b), C, M, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), C, M, 0xf, false);
+    v += __builtin_bit_cast(double, (long long)(unsigned(lo)) | ((long long)hi << 32));
+  };
+  using std::integral_constant;
+  add(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});   // row_shr:1
+  add(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});   // row_shr:2
+  add(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});   // row_shr:4
+  add(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});   // row_shr:8
+  add(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});   // row_bcast:15 into rows 1 and 3
+  add(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// Sum nf <= 24 values over the workgroup in a fixed order (deterministic): within each
+// wave, then wave results in wave order.  Thread f < nf returns field f.
 template <int NF>
 __device__ __forceinline__ double block_sum_fields(const double (&v)[NF], int nf, double* red) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -203,10 +227,8 @@ __device__ __forceinline__ double block_sum_fields(const double (&v)[NF], int nf
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
     if (f < nf) {
-      double s = v[f];
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-      if (lane == 0) red[wave * NF + f] = s;
+      const double s = wave_sum(v[f]);
+      if (lane == 63) red[wave * NF + f] = s;
     }
   }
   __syncthreads();
@@ -301,32 +323,52 @@ __device__ __forceinline__ void prescribed(const DevCase<L, St>& c, int x, int y
 }
 
 // Second pass of the volume reductions: sum the pending partials of an earlier launch
-// in a fixed order (deterministic) into c.pend_dest.  Run by one whole workgroup.
-template <class Case>
-__device__ __forceinline__ void fold_pending(const Case& c, double* red) {
-  constexpr int NF = kMaxLabels * 12;
-  const int nf = c.nl * 12;
-  const int nb = c.pend_nb;
-  double v[NF];
-#pragma unroll
-  for (int f = 0; f < NF; ++f) v[f] = 0.0;
-  for (int b = threadIdx.x; b < nb; b += blockDim.x) {
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-      if (f < nf) v[f] += c.part_r[long(f) * nb + b];
-  }
-  const double s = block_sum_fields<NF>(v, nf, red);
-  if (int(threadIdx.x) < nf) {
-    const int k = threadIdx.x / 12, f = threadIdx.x % 12;
-    c.pend_dest[k * kObsFields + f] = s;
-    if (f == 0) c.pend_dest[k * kObsFields + 12] = double(c.pend_step);
-  }
-  __syncthreads();
-}
+// in a fixed order (deterministic) into c.pend_dest.  fold_pending: by one whole
+// workgroup, a wave per group of six fields, with no barrier; a group's loads are in
+// flight together.
 template <class Case>
 __device__ __forceinline__ void fold_pending(const Case& c) {
-  __shared__ double red[16 * kMaxLabels * 12];
-  fold_pending(c, red);
+  constexpr int G = 6;
+  const int nf = c.nl * 12;   // a multiple of G
+  const int nb = c.pend_nb;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int nw = (blockDim.x + 63) >> 6;
+  for (int f0 = wave * G; f0 < nf; f0 += nw * G) {
+    double v[G];
+#pragma unroll
+    for (int j = 0; j < G; ++j) v[j] = 0.0;
+#pragma unroll 4
+    for (int b = lane; b < nb; b += 64) {
+#pragma unroll
+      for (int j = 0; j < G; ++j) v[j] += ldg(c.part_r + long(f0 + j) * nb, b);
+    }
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+      v[j] = wave_sum(v[j]);
+      if (lane == 63) {
+        const int k = (f0 + j) / 12, m = (f0 + j) % 12;
+        c.pend_dest[k * kObsFields + m] = v[j];
+        if (m == 0) c.pend_dest[k * kObsFields + 12] = double(c.pend_step);
+      }
+    }
+  }
+}
+// one field of one label by one whole workgroup (field 0 also notes the step)
+template <class Case>
+__device__ __forceinline__ void fold_field(const Case& c, int k, int j) {
+  __shared__ double red[16];
+  double v = 0.0;
+#pragma unroll 8
+  for (int b = threadIdx.x; b < c.pend_nb; b += blockDim.x) v += ldg(c.part_r + long(k * 12 + j) * c.pend_nb, b);
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    v = 0.0;
+    for (int w = 0; w < int(blockDim.x >> 6); ++w) v += red[w];
+    c.pend_dest[k * kObsFields + j] = v;
+    if (j == 0) c.pend_dest[k * kObsFields + 12] = double(c.pend_step);
+  }
 }
 
 // XCD-aware tile order: workgroups are dispatched round-robin over the 8 XCDs, so

@@ -44,7 +44,8 @@ namespace vclb {
 // opp(i) = i + 2 at s0 + 2n), directions 4, 7, 8 from the plane of opp(i) = i - 2 (their
 // own entry lies 2 ns further on; a bounce from the top wall reads s0 there).  ps
 // (shifted storage): the phi the stored deviations refer to, this node's own phis entry.
-template <class St>
+// NT: population loads with the non-temporal hint.
+template <class St, bool NT = false>
 __device__ __forceinline__ void pull9_flat(const typename St::S* const (&src)[9], const float* __restrict__ phis,
                                            int x, int y, int nx, int ny, int ns, bool wall,
                                            typename St::R (&v)[9], typename St::R* ps) {
@@ -68,7 +69,7 @@ __device__ __forceinline__ void pull9_flat(const typename St::S* const (&src)[9]
   }
   const typename St::S* base[9] = {src[0], src[1], src[2], src[3], src[2], src[5], src[6], src[5], src[6]};
 #pragma unroll
-  for (int i = 0; i < 9; ++i) v[i] = St::load(base[i], off[i]);
+  for (int i = 0; i < 9; ++i) v[i] = NT ? St::load_nt(base[i], off[i]) : St::load(base[i], off[i]);
   if constexpr (St::shifted) {   // every deviation refers to this node's own phis entry
     if (ps) {
       const R own = R(ldg(phis, s0));

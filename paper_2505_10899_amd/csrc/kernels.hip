@@ -352,15 +352,15 @@ __global__ void __launch_bounds__(BS, (step2d_min_blocks<St, UNIT, BS>()))
 
 // ---------------------------------------------------------------- second reduction pass
 // Stand-alone second pass (the fused steps instead fold the previous launch's partials
-// in their first workgroup).
+// in their first workgroups): a workgroup per field.
 template <class L, class St>
 __global__ void __launch_bounds__(256) k_finalize(DevCase<L, St> c) {
-  fold_pending(c);
+  fold_field(c, blockIdx.x / 12, blockIdx.x % 12);
 }
 
 template <class L, class St>
 int launch_finalize(const DevCase<L, St>& c, hipStream_t s) {
-  hipLaunchKernelGGL((k_finalize<L, St>), dim3(1), dim3(256), 0, s, c);
+  hipLaunchKernelGGL((k_finalize<L, St>), dim3(unsigned(c.nl * 12)), dim3(256), 0, s, c);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
@@ -395,6 +395,7 @@ int launch_step_plain(const DevCase<L, St>& c, int reduce, hipStream_t s) {
 template <class L, class St, bool COUPLED>
 int launch_step_fused(const DevCase<L, St>& c, const Tile& tile, int reduce, hipStream_t s) {
   if constexpr (L::D == 2) {
+    if (tile.lx > 0) return launch_tile2d<St, COUPLED>(c, tile.lx, tile.ly, reduce, s);
     const int nstrips = (c.nx + tile.bx - 1) / tile.bx;
     const int nseg = (c.ny + tile.ty - 1) / tile.ty;
     const size_t lds = size_t(2) * 4 * (tile.bx + 2) * sizeof(typename St::R);

@@ -435,8 +435,7 @@ __global__ void __launch_bounds__(BS, (step3d_min_blocks<St, BS>())) k_step3d(De
 #pragma unroll
     for (int i = 0; i < Q; ++i) g[i] = d[i * nthr];
   };
-  // the ring's LDS serves as reduction scratch before the march and after it
-  if (blockIdx.x == 0 && c.pend_nb > 0) fold_pending(c, reinterpret_cast<double*>(smem_raw));
+  if (blockIdx.x == 0 && c.pend_nb > 0) fold_pending(c);
   // reductions: the lane's (x, y) is fixed, so per label only sum phi, sum phi dz,
   // sum phi dz^2 and the counts are accumulated; the x and y moments follow at the end
   double s0[NL], s1[NL], s2[NL];

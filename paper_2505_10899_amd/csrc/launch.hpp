@@ -12,6 +12,10 @@ struct Tile {
   int bx = 256;
   int ty = 32;
   int by3 = 4;
+  // D2Q9: with lx > 0 the step runs one lane per node in tiles of 2^lx x 2^ly nodes
+  // (tile2d.hip) and bx, ty are only what a march would use
+  int lx = 0;
+  int ly = 0;
 };
 
 template <class L, class St, bool COUPLED>
@@ -20,6 +24,17 @@ template <class L, class St, bool COUPLED>
 int launch_step_plain(const DevCase<L, St>& c, int reduce, hipStream_t s);
 template <class L, class St, bool COUPLED>
 int launch_step_fused(const DevCase<L, St>& c, const Tile& tile, int reduce, hipStream_t s);
+// D2Q9 tiles of 2^lx x 2^ly nodes, one lane per node (tile2d.hip): 16 x 8 with a helper
+// wave, or 256 or 512 lanes.  The halo ring has at most a cell per lane.
+inline bool tile2d_helper(int lx, int ly) { return lx + ly == 7; }
+constexpr int tile2d_ring(int lanes) { return lanes + lanes / 2 + 16; }
+inline bool tile2d_shape_ok(int lx, int ly) {
+  if (lx < 1 || ly < 1 || lx + ly < 7 || lx + ly > 9) return false;
+  const int tx = 1 << lx, ty = 1 << ly, lanes = tx * ty;
+  return 2 * (tx + 2) + 2 * ty <= lanes && (tx + 2) * (ty + 2) <= tile2d_ring(lanes);
+}
+template <class St, bool COUPLED>
+int launch_tile2d(const DevCase<D2Q9, St>& c, int lx, int ly, int reduce, hipStream_t s);
 template <class L, class St, bool COUPLED>
 int launch_observe(const DevCase<L, St>& c, unsigned mask, double* out, hipStream_t s);
 template <class L, class St>
@@ -98,6 +113,7 @@ inline int flat_ring_cap(int nx, int B, int lag) {
 
 // number of workgroups the fused step launches for a case of this shape
 inline long fused_blocks(int dim, int nx, int ny, int nz, const Tile& t) {
+  if (dim == 2 && t.lx > 0) return long((nx + (1 << t.lx) - 1) >> t.lx) * ((ny + (1 << t.ly) - 1) >> t.ly);
   if (dim == 2) return long((nx + t.bx - 1) / t.bx) * ((ny + t.ty - 1) / t.ty);
   return long((nx + t.bx - 1) / t.bx) * ((ny + t.by3 - 1) / t.by3) * ((nz + t.ty - 1) / t.ty);
 }

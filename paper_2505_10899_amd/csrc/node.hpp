@@ -701,14 +701,28 @@ __device__ __forceinline__ void node_update_any(const NodeParams<L, R>& p, bool 
   else node_update<L, R, COUPLED, SH, false>(p, in, g, f, J, out);
 }
 // Velocity of the prescribed single vortex, Eqs. 43-44, at node (x, y) and step t.
+// factors of one axis (node i of n) and of the step
 template <class R>
-__device__ __forceinline__ void vortex_u(R U0, double T, int x, int y, int nx, int ny, long t, R& ux, R& uy) {
+__device__ __forceinline__ void vortex_factors(int i, int n, R& s1, R& s2) {
   const R pi = R(3.14159265358979323846);
-  const R sx = sin(pi * R(x) / R(nx)), sy = sin(pi * R(y) / R(ny));
-  const R s2x = sin(R(2) * pi * R(x) / R(nx)), s2y = sin(R(2) * pi * R(y) / R(ny));
-  const R ct = R(cos(3.14159265358979323846 * double(t) / T));
+  s1 = sin(pi * R(i) / R(n));
+  s2 = sin(R(2) * pi * R(i) / R(n));
+}
+template <class R>
+__device__ __forceinline__ R vortex_phase(double T, long t) {
+  return R(cos(3.14159265358979323846 * double(t) / T));
+}
+template <class R>
+__device__ __forceinline__ void vortex_from_factors(R U0, R sx, R s2x, R sy, R s2y, R ct, R& ux, R& uy) {
   ux = U0 * (sx * sx) * s2y * ct;
   uy = -U0 * (sy * sy) * s2x * ct;
+}
+template <class R>
+__device__ __forceinline__ void vortex_u(R U0, double T, int x, int y, int nx, int ny, long t, R& ux, R& uy) {
+  R sx, s2x, sy, s2y;
+  vortex_factors<R>(x, nx, sx, s2x);
+  vortex_factors<R>(y, ny, sy, s2y);
+  vortex_from_factors<R>(U0, sx, s2x, sy, s2y, vortex_phase<R>(T, t), ux, uy);
 }
 
 }  // namespace vclb
