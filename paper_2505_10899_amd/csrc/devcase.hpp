@@ -218,6 +218,43 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// The sums of four values over the wave, of v[i] in lane 16 i + 15.  Two swap steps fold
+// lane i + 32 into lane i and row 1 into row 0 for two values at a time, so that one
+// register carries the four rows' sums through the last four steps: a third of the
+// instructions of four wave sums.  Every lane of the wave must be active.
+__device__ __forceinline__ double wave_sum4(double v0, double v1, double v2, double v3) {
+  auto lo = [](double x) { return unsigned(__builtin_bit_cast(unsigned long long, x)); };
+  auto hi = [](double x) { return unsigned(__builtin_bit_cast(unsigned long long, x) >> 32); };
+  auto join = [](unsigned l, unsigned h) {
+    return __builtin_bit_cast(double, (unsigned long long)(l) | ((unsigned long long)h << 32));
+  };
+  // lanes below 32: a[i] + a[i + 32], the others: b[i - 32] + b[i]
+  auto halves = [&](double a, double b) {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo(a), lo(b), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi(a), hi(b), false, false);
+    return join(l[0], h[0]) + join(l[1], h[1]);
+  };
+  // even rows: a[row] + a[row + 1], odd rows: b[row - 1] + b[row]
+  auto rows = [&](double a, double b) {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo(a), lo(b), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi(a), hi(b), false, false);
+    return join(l[0], h[0]) + join(l[1], h[1]);
+  };
+  double v = rows(halves(v0, v2), halves(v1, v3));
+  auto add = [&](auto ctrl) {
+    constexpr int C = decltype(ctrl)::value;
+    const int l = __builtin_amdgcn_update_dpp(0, int(lo(v)), C, 0xf, 0xf, false);
+    const int h = __builtin_amdgcn_update_dpp(0, int(hi(v)), C, 0xf, 0xf, false);
+    v += join(unsigned(l), unsigned(h));
+  };
+  using std::integral_constant;
+  add(integral_constant<int, 0x111>{});   // row_shr:1
+  add(integral_constant<int, 0x112>{});   // row_shr:2
+  add(integral_constant<int, 0x114>{});   // row_shr:4
+  add(integral_constant<int, 0x118>{});   // row_shr:8
+  return v;
+}
+
 // Sum nf <= 24 values over the workgroup in a fixed order (deterministic): within each
 // wave, then wave results in wave order.  Thread f < nf returns field f.
 template <int NF>
@@ -225,10 +262,11 @@ __device__ __forceinline__ double block_sum_fields(const double (&v)[NF], int nf
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int nw = (blockDim.x + 63) >> 6;
 #pragma unroll
-  for (int f = 0; f < NF; ++f) {
+  for (int f = 0; f < NF; f += 4) {
     if (f < nf) {
-      const double s = wave_sum(v[f]);
-      if (lane == 63) red[wave * NF + f] = s;
+      auto at = [&](int j) { return j < NF ? v[j < NF ? j : 0] : 0.0; };
+      const double s = wave_sum4(at(f), at(f + 1), at(f + 2), at(f + 3));
+      if ((lane & 15) == 15 && f + (lane >> 4) < NF) red[wave * NF + f + (lane >> 4)] = s;
     }
   }
   __syncthreads();
@@ -324,11 +362,11 @@ __device__ __forceinline__ void prescribed(const DevCase<L, St>& c, int x, int y
 
 // Second pass of the volume reductions: sum the pending partials of an earlier launch
 // in a fixed order (deterministic) into c.pend_dest.  fold_pending: by one whole
-// workgroup, a wave per group of six fields, with no barrier; a group's loads are in
+// workgroup, a wave per group of four fields, with no barrier; a group's loads are in
 // flight together.
 template <class Case>
 __device__ __forceinline__ void fold_pending(const Case& c) {
-  constexpr int G = 6;
+  constexpr int G = 4;
   const int nf = c.nl * 12;   // a multiple of G
   const int nb = c.pend_nb;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -342,33 +380,45 @@ __device__ __forceinline__ void fold_pending(const Case& c) {
 #pragma unroll
       for (int j = 0; j < G; ++j) v[j] += ldg(c.part_r + long(f0 + j) * nb, b);
     }
-#pragma unroll
-    for (int j = 0; j < G; ++j) {
-      v[j] = wave_sum(v[j]);
-      if (lane == 63) {
-        const int k = (f0 + j) / 12, m = (f0 + j) % 12;
-        c.pend_dest[k * kObsFields + m] = v[j];
-        if (m == 0) c.pend_dest[k * kObsFields + 12] = double(c.pend_step);
-      }
+    const double s = wave_sum4(v[0], v[1], v[2], v[3]);
+    if ((lane & 15) == 15) {
+      const int j = f0 + (lane >> 4), k = j / 12, m = j % 12;
+      c.pend_dest[k * kObsFields + m] = s;
+      if (m == 0) c.pend_dest[k * kObsFields + 12] = double(c.pend_step);
     }
   }
 }
-// one field of one label by one whole workgroup (field 0 also notes the step)
-template <class Case>
-__device__ __forceinline__ void fold_field(const Case& c, int k, int j) {
+// one field j of label k by one whole workgroup (field 0 also notes the step): partials
+// [label * 12 + field][nb] into dest[label][kObsFields]
+__device__ __forceinline__ void fold_field(const double* __restrict__ part, int nb, double* __restrict__ dest,
+                                           long step, int k, int j) {
   __shared__ double red[16];
   double v = 0.0;
 #pragma unroll 8
-  for (int b = threadIdx.x; b < c.pend_nb; b += blockDim.x) v += ldg(c.part_r + long(k * 12 + j) * c.pend_nb, b);
+  for (int b = threadIdx.x; b < nb; b += blockDim.x) v += ldg(part + long(k * 12 + j) * nb, b);
   v = wave_sum(v);
   if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
     v = 0.0;
     for (int w = 0; w < int(blockDim.x >> 6); ++w) v += red[w];
-    c.pend_dest[k * kObsFields + j] = v;
-    if (j == 0) c.pend_dest[k * kObsFields + 12] = double(c.pend_step);
+    dest[k * kObsFields + j] = v;
+    if (j == 0) dest[k * kObsFields + 12] = double(step);
   }
+}
+template <class Case>
+__device__ __forceinline__ void fold_field(const Case& c, int k, int j) {
+  fold_field(c.part_r, c.pend_nb, c.pend_dest, c.pend_step, k, j);
+}
+
+// Chunks of the stand-alone reductions of a state of n nodes: 1024 nodes each (four per
+// lane), more from 4 Mi nodes on, so that the second pass sums at most 4096 partials.  They
+// depend on n alone: a case gives the same sums by itself and in a batch.
+__host__ __device__ constexpr long reduce_chunk_nodes(long n) {
+  return n <= (4096L << 10) ? 1024 : (n + (4096L * 256 - 1)) / (4096L * 256) * 256;
+}
+__host__ __device__ constexpr long reduce_blocks(long n) {
+  return (n + reduce_chunk_nodes(n) - 1) / reduce_chunk_nodes(n);
 }
 
 // XCD-aware tile order: workgroups are dispatched round-robin over the 8 XCDs, so

@@ -309,17 +309,48 @@ __global__ void __launch_bounds__(256) k_fields(DevCase<L, St> c, unsigned mask,
   if (mask & 0x20u) { out[off + n] = double(in.npsi[0]); off += c.n; }
 }
 
-// reductions of the current state (phi from scratch), into c.cur
+// ---------------------------------------------------------------- reductions of a state
+// Partial reductions of the nodes of chunk b, phi formed from the pulled populations on
+// the way: one read of g and nothing written but the sums (a pass that stored phi and psi
+// and another that read phi, with a workgroup sum of 12 or 24 values for every 256 nodes,
+// took 980 us on 4096 x 4096 FP32, where reading g takes 115).
 template <class L, class St>
-__global__ void __launch_bounds__(256) k_reduce_state(DevCase<L, St> c) {
-  const long n = blockIdx.x * long(blockDim.x) + threadIdx.x;
+__device__ __forceinline__ void reduce_chunk(const DevCase<L, St>& c, long t, long b, long nb, long chunk) {
+  using R = typename St::R;
+  const int par = int(t & 1);
   Acc acc;
   acc.zero();
-  if (n < c.n) {
-    const int x = int(n % c.nx), y = int((n / c.nx) % c.ny), z = int(n / (long(c.nx) * c.ny));
-    accumulate(c, acc, double(c.tmp_phi[n]), x, y, z);
+  const long hi = min(c.n, (b + 1) * chunk);
+  for (long n = b * chunk + threadIdx.x; n < hi; n += blockDim.x) {
+    const unsigned row = unsigned(n) / unsigned(c.nx);   // n < 2^31
+    const int x = int(unsigned(n) - row * unsigned(c.nx)), z = int(row / unsigned(c.ny)),
+              y = int(row - unsigned(z) * unsigned(c.ny));
+    R g[L::Q], ps[L::Q];
+    pull<L, St>(c, c.pop[0][par], c.phis[par], x, y, z, g, ps);
+    accumulate(c, acc, double(phi_of_pulled<L, St>(g, ps, c.np.rest)), x, y, z);
   }
-  finish_block(c, acc, true);
+  write_partials(acc, c.nl, c.part_w, nb, b);
+}
+
+template <class L, class St>
+__global__ void __launch_bounds__(256) k_reduce_state(DevCase<L, St> c, long chunk) {
+  reduce_chunk(c, c.t, blockIdx.x, gridDim.x, chunk);
+}
+
+// every case of a batch in one launch: blocks[i] = (case, chunk of that case)
+template <class St>
+__global__ void __launch_bounds__(256) k_batch_reduce(const DevCase<D2Q9, St>* __restrict__ cases,
+                                                      const int2* __restrict__ blocks, long t) {
+  const int2 w = blocks[blockIdx.x];
+  const DevCase<D2Q9, St>& c = cases[w.x];
+  reduce_chunk(c, t, w.y, reduce_blocks(c.n), reduce_chunk_nodes(c.n));
+}
+// its second pass, a workgroup per case and field: out[case][field]
+template <class St>
+__global__ void __launch_bounds__(256) k_batch_reduce_fold(const DevCase<D2Q9, St>* __restrict__ cases,
+                                                           double* __restrict__ out, long t) {
+  const int k = blockIdx.x / 12;
+  fold_field(cases[k].part_w, int(reduce_blocks(cases[k].n)), out + long(k) * kObsFields, t, 0, blockIdx.x % 12);
 }
 
 // ---------------------------------------------------------------- fused 2D step (A1-A11)
@@ -471,12 +502,23 @@ int launch_mass_ref(const DevCase<L, St>& c, hipStream_t s) {
 
 template <class L, class St>
 int launch_reduce_state(const DevCase<L, St>& c, hipStream_t s) {
-  const unsigned nb = unsigned((c.n + 255) / 256);
-  hipLaunchKernelGGL((k_phi_psi<L, St>), dim3(nb), dim3(256), 0, s, c);
-  hipLaunchKernelGGL((k_reduce_state<L, St>), dim3(nb), dim3(256), 0, s, c);
+  const unsigned nb = unsigned(reduce_blocks(c.n));
+  hipLaunchKernelGGL((k_reduce_state<L, St>), dim3(nb), dim3(256), 0, s, c, reduce_chunk_nodes(c.n));
   launch_finalize(self_pending(c, int(nb), c.cur), s);
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
+
+template <class St>
+int launch_batch_reduce(const void* cases, int ncases, const int2* blocks, int nblocks, long t, double* out,
+                        hipStream_t s) {
+  const auto* cs = static_cast<const DevCase<D2Q9, St>*>(cases);
+  hipLaunchKernelGGL((k_batch_reduce<St>), dim3(unsigned(nblocks)), dim3(256), 0, s, cs, blocks, t);
+  hipLaunchKernelGGL((k_batch_reduce_fold<St>), dim3(unsigned(ncases) * 12), dim3(256), 0, s, cs, out, t);
+  return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+template int launch_batch_reduce<StoreF64>(const void*, int, const int2*, int, long, double*, hipStream_t);
+template int launch_batch_reduce<StoreF32>(const void*, int, const int2*, int, long, double*, hipStream_t);
+template int launch_batch_reduce<StoreF16S>(const void*, int, const int2*, int, long, double*, hipStream_t);
 
 template <class L, class St, bool COUPLED>
 int launch_set_state(const DevCase<L, St>& c, const double* g, const double* f, const double* J, long t,

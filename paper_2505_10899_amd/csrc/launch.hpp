@@ -25,14 +25,9 @@ int launch_step_plain(const DevCase<L, St>& c, int reduce, hipStream_t s);
 template <class L, class St, bool COUPLED>
 int launch_step_fused(const DevCase<L, St>& c, const Tile& tile, int reduce, hipStream_t s);
 // D2Q9 tiles of 2^lx x 2^ly nodes, one lane per node (tile2d.hip): 16 x 8 with a helper
-// wave, or 256 or 512 lanes.  The halo ring has at most a cell per lane.
-inline bool tile2d_helper(int lx, int ly) { return lx + ly == 7; }
-constexpr int tile2d_ring(int lanes) { return lanes + lanes / 2 + 16; }
-inline bool tile2d_shape_ok(int lx, int ly) {
-  if (lx < 1 || ly < 1 || lx + ly < 7 || lx + ly > 9) return false;
-  const int tx = 1 << lx, ty = 1 << ly, lanes = tx * ty;
-  return 2 * (tx + 2) + 2 * ty <= lanes && (tx + 2) * (ty + 2) <= tile2d_ring(lanes);
-}
+// wave, 64 x 4 and 128 x 4
+inline bool tile2d_helper(int lx, int ly) { return lx == 4; }
+inline bool tile2d_shape_ok(int lx, int ly) { return (lx == 4 && ly == 3) || ((lx == 6 || lx == 7) && ly == 2); }
 template <class St, bool COUPLED>
 int launch_tile2d(const DevCase<D2Q9, St>& c, int lx, int ly, int reduce, hipStream_t s);
 template <class L, class St, bool COUPLED>
@@ -55,6 +50,12 @@ template <class St>
 int launch_step3d(const DevCase<D3Q19, St>& c, const Tile& tile, int reduce, hipStream_t s);
 template <class St>
 size_t step3d_lds_bytes(int bx, int by3);   // LDS of the fused 3D step for a bx x by3 section
+
+// reductions of the current state (time level t) of every case of a batch: blocks[i] =
+// (case, chunk) for the reduce_blocks chunks of each case; out[case][kObsFields]
+template <class St>
+int launch_batch_reduce(const void* cases, int ncases, const int2* blocks, int nblocks, long t, double* out,
+                        hipStream_t s);
 
 struct BatchArgs {
   const int4* items;        // (case, x0, y0, y1) of every work item, case-major; x0 < 0: a

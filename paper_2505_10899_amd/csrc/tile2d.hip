@@ -24,15 +24,15 @@
 
 namespace vclb {
 
-// BS: lanes of the tile.  HELP: one more wave, which pulls the first 64 halo cells and
+// LX, LY: log2 of the tile's sides.  HELP: one more wave, which pulls the first 64 halo cells and
 // sums the tile's reductions while the others update.  That takes both off the critical
 // path of a step that waits for one launch (128 x 128 FP64: 7.4 -> 5.9 us, of which the
 // reductions now cost 0.6), but a wave in three idles; large grids, which need every wave
 // (1501 x 1003 FP16S: 27.7 -> 31.3 us), leave both to the tile's own lanes.
 // NT: stores of the populations and loads of f with the non-temporal hint.
-template <class St, bool COUPLED, bool UNIT, bool VISC, int BS, bool HELP, bool NT>
-__global__ void __launch_bounds__(HELP ? BS + 64 : BS)
-    k_tile2d(DevCase<D2Q9, St> c, int lx, int ly, int ntx, int ntiles, int reduce) {
+template <class St, bool COUPLED, bool UNIT, bool VISC, int LX, int LY, bool HELP, bool NT>
+__global__ void __launch_bounds__((1 << (LX + LY)) + (HELP ? 64 : 0))
+    k_tile2d(DevCase<D2Q9, St> c, int ntx, int ntiles, int reduce) {
   using L = D2Q9;
   using R = typename St::R;
   using S = typename St::S;
@@ -55,16 +55,17 @@ __global__ void __launch_bounds__(HELP ? BS + 64 : BS)
   struct alignas(2 * sizeof(R)) PhiPsi {
     R phi, psi;
   };
-  // the tile and its halo ring: (TX + 2)(TY + 2) nodes (the launcher checks the shape)
-  __shared__ PhiPsi ring[tile2d_ring(BS)];
+  constexpr int TX = 1 << LX, TY = 1 << LY, PW = TX + 2, nodes = TX * TY;
+  constexpr int nring = 2 * PW + 2 * TY;   // halo cells
+  static_assert(nring <= nodes && nodes % 64 == 0, "a halo cell per lane");
+  __shared__ PhiPsi ring[PW * (TY + 2)];   // the tile and its halo
   const int tile = xcd_tile(int(blockIdx.x) - extra, ntiles);
   const int ty_i = tile / ntx, tx_i = tile - ty_i * ntx;
-  const int TX = 1 << lx, TY = 1 << ly, PW = TX + 2, nodes = TX * TY;
   const int nx = c.nx, ny = c.ny, ns = int(c.ns);
-  const int x0 = tx_i << lx, y0 = ty_i << ly;
+  const int x0 = tx_i * TX, y0 = ty_i * TY;
   const int tid = threadIdx.x;
   const bool helper = HELP && tid >= nodes;   // the last wave has no node of its own
-  const int tx = tid & (TX - 1), ty = tid >> lx;
+  const int tx = tid % TX, ty = tid / TX;
   const int xg = x0 + tx, yg = y0 + ty;
   const bool active = !helper && xg < nx && yg < ny;
   const bool wall = c.wall != 0;
@@ -91,7 +92,6 @@ __global__ void __launch_bounds__(HELP ? BS + 64 : BS)
   R g[Q], ps[Q], f[Q], J[2], gh[Q], hps[Q];
   if (!helper) pull9_flat<St>(gsrc, phis, xw, yw, nx, ny, ns, wall, g, ps);
   // halo cells, one per lane: the helper wave first, then the tile's lanes from lane 0
-  const int nring = 2 * PW + 2 * TY;
   const int cell = !HELP ? tid : (helper ? tid - nodes : tid + 64);
   int px = 0, py = 0;
   if (cell < nring) {
@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(HELP ? BS + 64 : BS)
   }
   // the vortex factors of the tile's columns, rows and the step, once per tile and not per
   // node: sin(pi x / nx), sin(2 pi x / nx) of column i at [i], of row i at [TX + i]
-  __shared__ R trig[COUPLED ? 1 : 2][COUPLED ? 1 : BS + 1];
+  __shared__ R trig[COUPLED ? 1 : 2][COUPLED ? 1 : TX + TY + 1];
   if constexpr (!COUPLED) {
     if (tid < TX) vortex_factors<R>(col_of(x0 + tid), nx, trig[0][tid], trig[1][tid]);
     else if (tid < TX + TY) vortex_factors<R>(row_of(y0 + tid - TX), ny, trig[0][tid], trig[1][tid]);
@@ -177,8 +177,11 @@ __global__ void __launch_bounds__(HELP ? BS + 64 : BS)
   // this tile's volume reductions, by one wave from the ring's phi: the helper, or the last
   // wave (the first ones pull the halo).  Six sums over the wave once per tile instead of
   // once per wave: 1501 x 1003 FP16S 34.9 -> 27.7 us.
-  if (!reduce || (HELP ? !helper : tid < nodes - 64)) return;
+  if (!reduce || tid < (HELP ? nodes : nodes - 64)) return;
+  // A lane keeps to a column (or two, TX = 128), so only phi, phi dy, phi dy^2 add up per
+  // node and the x moments follow.
   const int lane = tid & 63;
+  constexpr int kCols = TX > 64 ? TX / 64 : 1, kRowStep = TX < 64 ? 64 / TX : 1;
   double s[kMaxLabels][6];
   int cnt[kMaxLabels], bad[kMaxLabels];
 #pragma unroll
@@ -187,42 +190,60 @@ __global__ void __launch_bounds__(HELP ? BS + 64 : BS)
 #pragma unroll
     for (int j = 0; j < 6; ++j) s[k][j] = 0.0;
   }
-  for (int n = lane; n < nodes; n += 64) {
-    const int rx = n & (TX - 1), ry = n >> lx, x = x0 + rx, y = y0 + ry;
-    const bool in = x < nx && y < ny;
-    const double ph = in ? double(ring[(ry + 1) * PW + rx + 1].phi) : 0.0;
-    double dx[kMaxLabels], dy[kMaxLabels];
+#pragma unroll
+  for (int h = 0; h < kCols; ++h) {
+    const int rx = lane % TX + 64 * h, x = x0 + rx;
+    double dx[kMaxLabels], s0[kMaxLabels], s1[kMaxLabels], s2[kMaxLabels];
 #pragma unroll
     for (int k = 0; k < kMaxLabels; ++k) {
       dx[k] = min_image(double(x) - c.cen[k][0], nx, true);
-      dy[k] = min_image(double(y) - c.cen[k][1], ny, !wall);
+      s0[k] = s1[k] = s2[k] = 0.0;
     }
-    const int lab = c.nl > 1 && dx[1] * dx[1] + dy[1] * dy[1] < dx[0] * dx[0] + dy[0] * dy[0] ? 1 : 0;
+#pragma unroll
+    for (int i = 0; i < TY / kRowStep; ++i) {
+      const int ry = lane / TX + i * kRowStep, y = y0 + ry;
+      const double ph = x < nx && y < ny ? double(ring[(ry + 1) * PW + rx + 1].phi) : 0.0;
+      double dy[kMaxLabels];
+#pragma unroll
+      for (int k = 0; k < kMaxLabels; ++k) dy[k] = min_image(double(y) - c.cen[k][1], ny, !wall);
+      const int lab = c.nl > 1 && dx[1] * dx[1] + dy[1] * dy[1] < dx[0] * dx[0] + dy[0] * dy[0] ? 1 : 0;
+#pragma unroll
+      for (int k = 0; k < kMaxLabels; ++k) {
+        if (k >= c.nl) break;
+        const double w = lab == k ? ph : 0.0;
+        s0[k] += w;
+        s1[k] += w * dy[k];
+        s2[k] += w * dy[k] * dy[k];
+        cnt[k] += __popcll(__ballot(lab == k && ph >= 0.5));
+        bad[k] += __popcll(__ballot(lab == k && !isfinite(ph)));
+      }
+    }
 #pragma unroll
     for (int k = 0; k < kMaxLabels; ++k) {
-      if (k >= c.nl) break;
-      const double w = lab == k ? ph : 0.0;
-      const double wx = w * dx[k], wy = w * dy[k];
-      s[k][0] += w;
-      s[k][1] += wx;
-      s[k][2] += wy;
-      s[k][3] += wx * dx[k];
-      s[k][4] += wy * dy[k];
-      s[k][5] += wx * dy[k];
-      cnt[k] += __popcll(__ballot(lab == k && ph >= 0.5));
-      bad[k] += __popcll(__ballot(lab == k && !isfinite(ph)));
+      s[k][0] += s0[k];
+      s[k][1] += dx[k] * s0[k];
+      s[k][2] += s1[k];
+      s[k][3] += dx[k] * dx[k] * s0[k];
+      s[k][4] += s2[k];
+      s[k][5] += dx[k] * s1[k];
     }
   }
+  // lane 16 i + 15 stores field i of each group of four
 #pragma unroll
   for (int k = 0; k < kMaxLabels; ++k) {
     if (k >= c.nl) break;
-#pragma unroll
-    for (int j = 0; j < 6; ++j) s[k][j] = wave_sum(s[k][j]);
-    if (lane == 63) {
-      const double v[12] = {s[k][0], double(cnt[k]), s[k][1], s[k][2], 0.0, s[k][3],
-                            s[k][4], 0.0,            s[k][5], 0.0,     0.0, double(bad[k])};
-#pragma unroll
-      for (int j = 0; j < 12; ++j) stg(c.part_w + long(k * 12 + j) * ntiles, tile, v[j]);
+    const double a = wave_sum4(s[k][0], s[k][1], s[k][2], s[k][3]);
+    double b = wave_sum4(s[k][4], s[k][5], 0.0, 0.0);
+    const int i = lane >> 4;
+    if (i >= 2) b = double(i == 2 ? cnt[k] : bad[k]);
+    if ((lane & 15) == 15) {
+      double* p = c.part_w + tile;
+      // fields: sum, count, x, y, z, xx, yy, zz, xy, xz, yz, not finite
+      const int fa = i == 0 ? 0 : (i == 1 ? 2 : (i == 2 ? 3 : 5)), fb = i == 0 ? 6 : (i == 1 ? 8 : (i == 2 ? 1 : 11));
+      const int fz = i == 0 ? 4 : (i == 1 ? 7 : (i == 2 ? 9 : 10));
+      stg(p, long(k * 12 + fa) * ntiles, a);
+      stg(p, long(k * 12 + fb) * ntiles, b);
+      stg(p, long(k * 12 + fz) * ntiles, 0.0);
     }
   }
 }
@@ -238,15 +259,15 @@ int launch_tile2d(const DevCase<D2Q9, St>& c, int lx, int ly, int reduce, hipStr
   // FP32 348 -> 420 us) of grids whose two population sets exceed the 256 MB last-level
   // cache (2048 x 2048 FP32 145 -> 131, FP64 268 -> 248; within it 1024 x 1024 FP32 29.5 -> 43)
   const size_t set = size_t(c.ns) * 9 * sizeof(typename St::S) * (COUPLED ? 4 : 2);
-  const bool nt = lanes == 512 && size_t(c.nx) * sizeof(typename St::S) % 128 == 0 && set > (size_t(256) << 20);
+  const bool nt = lx == 7 && size_t(c.nx) * sizeof(typename St::S) % 128 == 0 && set > (size_t(256) << 20);
   const dim3 grid(unsigned(ntiles + (c.pend_nb > 0 ? c.nl * 8 : 0))), block(unsigned(lanes + (help ? 64 : 0)));
   auto go = [&](auto unit, auto visc) {
     constexpr bool U = decltype(unit)::value, V = decltype(visc)::value;
-    auto run = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, s, c, lx, ly, ntx, ntiles, reduce); };
-    if (help) run(k_tile2d<St, COUPLED, U, V, 128, true, false>);
-    else if (lanes == 256) run(k_tile2d<St, COUPLED, U, V, 256, false, false>);
-    else if (nt) run(k_tile2d<St, COUPLED, U, V, 512, false, true>);
-    else run(k_tile2d<St, COUPLED, U, V, 512, false, false>);
+    auto run = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, s, c, ntx, ntiles, reduce); };
+    if (help) run(k_tile2d<St, COUPLED, U, V, 4, 3, true, false>);
+    else if (lx == 6) run(k_tile2d<St, COUPLED, U, V, 6, 2, false, false>);
+    else if (nt) run(k_tile2d<St, COUPLED, U, V, 7, 2, false, true>);
+    else run(k_tile2d<St, COUPLED, U, V, 7, 2, false, false>);
   };
   auto pick_visc = [&](auto unit) {
     if constexpr (COUPLED) {
