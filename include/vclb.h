@@ -208,7 +208,9 @@ int vclb_case_create(const vclb_params* p, void* workspace, size_t workspace_byt
                      vclb_case** out);
 void vclb_case_destroy(vclb_case* c);
 
-/* Tile of the fused step kernel.  D2Q9: bx lanes (x columns; a multiple of 64 in
+/* Tile of the fused step kernel.  By default a D2Q9 case that the march below would leave
+   waiting for its row round trips steps in tiles of one lane per node instead; get_tile
+   returns the march's shape all the same, and set_tile chooses the march.  D2Q9: bx lanes (x columns; a multiple of 64 in
    64..256, or 512 or 1024 with FP32 or FP16S storage) marching ty >= 1 rows of y (by3
    ignored).  D3Q19: a bx x by3 section of (x, y)
    columns (bx * by3 a multiple of 64, at most 256, or at most 768 with FP32 or FP16S
@@ -223,7 +225,8 @@ int vclb_case_get_tile(const vclb_case* c, int32_t* bx, int32_t* ty, int32_t* by
    or take it from the JSON-lines file cache_path when that holds an entry for this case's
    lattice, storage, mode, shape, boundary and label count; a measured choice is appended
    to cache_path (NULL: no file).  D2Q9 candidates: bx in {64, 128, 256} (and 512, 1024
-   with 4-byte storage) x ty in {8, ..., 128}; D3Q19: six column sections with their
+   with 4-byte storage) x ty in {8, ..., 128}, and, for a case that steps in tiles of one
+   lane per node by default, three such tiles; D3Q19: six column sections with their
    planes cut to fill 1..4 workgroups per CU, and (4-byte storage) three 768-lane
    sections at one per CU.  Synchronises the stream; VCLB_ESTATE before init. */
 int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void* stream);
@@ -363,9 +366,8 @@ int vclb_adjoint_run(vclb_case* c, const double* seed, double normal_tau, double
 
 /* ---------------------------------------------------------------- batches of cases */
 /* Many independent coupled D2Q9 cases of uneven sizes (one storage precision), advanced
-   together: each step is one work-list kernel over the tiles of every case, and a call
-   of vclb_batch_step captures its steps in one hipGraph replayed as one launch.  The
-   batch owns one device allocation holding every case. */
+   together: each step is one kernel over the tiles of every case, or over balanced runs of
+   work items.  The batch owns one device allocation holding every case. */
 typedef struct vclb_batch vclb_batch;
 
 /* Validate every case (all VCLB_D2Q9, VCLB_COUPLED, one storage, nlabels <= 1, no global
@@ -398,7 +400,10 @@ int vclb_batch_nodes(const vclb_batch* b, int64_t* nodes);
    whole).  As many workgroups as can be resident are launched, each given one run of
    consecutive items with about equal work, or work in proportion to the slot weights
    vclb_batch_balance measured (an item is split between rows where a run ends);
-   get_tile also returns that workgroup count.  Default: bx 512, ty 1024. */
+   get_tile also returns that workgroup count.  Default: bx 512, ty 1024; a batch whose
+   population sets fit the last-level cache together (256 MB) first steps in tiles of one
+   lane per node instead, until set_tile or set_schedule chooses a run shape (or autotune
+   finds one faster). */
 int vclb_batch_set_tile(vclb_batch* b, int32_t bx, int32_t ty);
 int vclb_batch_get_tile(const vclb_batch* b, int32_t* bx, int32_t* ty, int32_t* blocks);
 
@@ -428,9 +433,10 @@ int vclb_batch_reduce(vclb_batch* b, vclb_obs* out, void* stream);
    steps or not recorded). */
 int vclb_batch_history(vclb_batch* b, int64_t t_first, int32_t count, vclb_obs* out, void* stream);
 
-/* Advance every case by nsteps (all cases must be initialised and at the same step).
-   use_graph != 0: the launches are captured into one hipGraph on a library stream
-   ordered after `stream`.  Asynchronous with respect to the host. */
+/* Advance every case by nsteps (all cases must be initialised and at the same step), one
+   launch per step on `stream`.  use_graph is kept for its callers: recording the launches
+   into a hipGraph per call was slower than launching them, so it only refuses
+   (VCLB_EHIP) a stream under capture.  Asynchronous with respect to the host. */
 int vclb_batch_step(vclb_batch* b, int64_t nsteps, int32_t use_graph, void* stream);
 
 /* Pick the batched tile and schedule (bx, ty, flat_pct) by timing `steps` steps of every
@@ -452,7 +458,8 @@ int vclb_batch_autotune(vclb_batch* b, const char* cache_path, int32_t steps, vo
    included; *gain (may be NULL) receives the slowest slot's time before over after
    (1 if nothing beat the cut it started from).  The results of a step do not depend on
    the cut (each node's update is the same); the per-case reductions are summed in
-   another grouping, so they may differ in the last bits.  The weights stay in force
+   another grouping, so they may differ in the last bits.  A batch in tiles of one lane per
+   node has no runs: nothing is timed and *gain is 1.  The weights stay in force
    while the launch shape is unchanged: set_tile or set_schedule with another shape, or
    autotune, drop them. */
 int vclb_batch_balance(vclb_batch* b, int32_t rounds, int32_t steps, double* gain, void* stream);

@@ -1254,10 +1254,12 @@ struct vclb_batch {
   bool pend = false;
   int pend_buf = 0;
   int64_t pend_step = 0;
-  hipStream_t own = nullptr;
-  hipEvent_t ev_in = nullptr, ev_out = nullptr;
-  hipGraphExec_t gexec = nullptr;
-  hipGraph_t graph = nullptr;
+  // the step in lane tiles of 2^lx x 2^ly nodes instead of runs of work items: the tables
+  // exist if lx > 0, `lane` says which is in force
+  bool lane = false;
+  int lx = 0, ly = 0, ntiles = 0;
+  int2* d_tiles = nullptr;            // (case, tile) of every workgroup
+  int2* d_tile_cases = nullptr;       // (first tile, tile count) per case
 };
 
 namespace {
@@ -1457,6 +1459,13 @@ int batch_set_tile(vclb_batch* b, int bx, int ty, int flat_pct) {
   return VCLB_OK;
 }
 
+// the caller's choice of a run shape: steps run in that shape from now on
+int batch_set_runs(vclb_batch* b, int bx, int ty, int flat_pct) {
+  const int rc = batch_set_tile(b, bx, ty, flat_pct);
+  if (!rc) b->lane = false;
+  return rc;
+}
+
 // modelled cost (march iterations) of each run slot of the current cut
 std::vector<double> run_costs(const vclb_batch* b) {
   std::vector<double> cost(b->runs.size(), 0.0);
@@ -1472,9 +1481,11 @@ std::vector<double> run_costs(const vclb_batch* b) {
 vclb::BatchArgs batch_args(const vclb_batch* b, int64_t t, int reduce) {
   vclb::BatchArgs a{};
   a.items = b->d_items;
-  a.nitems = int(b->items.size());
+  a.nitems = b->lane ? b->ntiles : int(b->items.size());
   a.runs = b->d_runs;
-  a.case_items = b->d_case_items;
+  a.case_items = b->lane ? b->d_tile_cases : b->d_case_items;
+  a.tiles = b->d_tiles;
+  a.ntiles = b->ntiles;
   a.ncases = b->n;
   a.part_w = b->part[t & 1];
   a.part_r = b->part[b->pend_buf];
@@ -1490,6 +1501,33 @@ vclb::BatchArgs batch_args(const vclb_batch* b, int64_t t, int reduce) {
   return a;
 }
 
+// Whether a batch steps in lane tiles (tile2d.hip), one workgroup per tile of every case,
+// and its tables; b->lx stays 0 if not.  They pay while every case's population sets fit
+// the 256 MB last-level cache together, where the runs leave CUs idle or wait for their
+// row round trips (us a step, runs / tiles: 4 cases of 35 k nodes in FP32 7.6 / 5.4, 24 of
+// 214 k in FP64 18.6 / 14.8, 68 of 1.36 M in FP32 53 / 42); beyond it the runs' single read
+// of each population wins (100 cases of 1.87 M nodes in FP32 70 / 99, 256 of 11.7 M in FP64
+// 778 / 1076).  Tiles of 64 x 4 were within 5% of 16 x 8 on every such batch.
+void batch_lane_tiles(vclb_batch* b, const vclb_params* cases, size_t items_cap, std::vector<int2>& tiles,
+                      std::vector<int2>& per_case) {
+  const int lx = 4, ly = 3;
+  if (size_t(b->nodes) * 9 * storage_bytes(b->storage) * 4 > (size_t(256) << 20)) return;
+  for (int k = 0; k < b->n; ++k) {
+    const int nt = ((cases[k].nx + (1 << lx) - 1) >> lx) * ((cases[k].ny + (1 << ly) - 1) >> ly);
+    per_case.push_back(int2{int(tiles.size()), nt});
+    for (int i = 0; i < nt; ++i) tiles.push_back(int2{k, i});
+    if (tiles.size() > items_cap) {   // more than the partial reductions hold
+      tiles.clear();
+      per_case.clear();
+      return;
+    }
+  }
+  b->lx = lx;
+  b->ly = ly;
+  b->ntiles = int(tiles.size());
+  b->lane = true;
+}
+
 // enqueue nsteps batched steps (and the closing fold) on stream s
 int batch_enqueue(vclb_batch* b, int64_t nsteps, bool reduce_on, hipStream_t s) {
   const int64_t t0 = b->cases[0]->t_host;
@@ -1498,7 +1536,9 @@ int batch_enqueue(vclb_batch* b, int64_t nsteps, bool reduce_on, hipStream_t s) 
     const int reduce = (reduce_on && b->reduce_every > 0 && t % b->reduce_every == 0) ? 1 : 0;
     const vclb::BatchArgs a = batch_args(b, t, reduce);
     int rc = dispatch_storage(b->storage, [&](auto st) {
-      return vclb::launch_batch_step<decltype(st)>(b->d_cases, a, b->blocks, b->bx, s);
+      using St = decltype(st);
+      return b->lane ? vclb::launch_batch_tile2d<St>(b->d_cases, a, b->lx, b->ly, s)
+                     : vclb::launch_batch_step<St>(b->d_cases, a, b->blocks, b->bx, s);
     });
     if (rc) return fail(VCLB_EHIP, "batched step launch failed");
     b->pend = reduce != 0;
@@ -1512,18 +1552,6 @@ int batch_enqueue(vclb_batch* b, int64_t nsteps, bool reduce_on, hipStream_t s) 
     b->pend = false;
   }
   return VCLB_OK;
-}
-
-void batch_release_graph(vclb_batch* b) {
-  if (b->gexec) {
-    (void)hipEventSynchronize(b->ev_out);
-    (void)hipGraphExecDestroy(b->gexec);
-    b->gexec = nullptr;
-  }
-  if (b->graph) {
-    (void)hipGraphDestroy(b->graph);
-    b->graph = nullptr;
-  }
 }
 
 }  // namespace
@@ -1590,6 +1618,12 @@ int vclb_batch_create(const vclb_params* cases, int32_t ncases, vclb_batch** out
   }
   const size_t o_reduce = total;
   total += align_up(chunks.size() * sizeof(int2));
+  std::vector<int2> tiles, tile_cases;
+  batch_lane_tiles(b, cases, cap, tiles, tile_cases);
+  const size_t o_tiles = total;
+  total += align_up(tiles.size() * sizeof(int2));
+  const size_t o_tc = total;
+  total += align_up(tile_cases.size() * sizeof(int2));
   const size_t o_cur = total;
   total += align_up(size_t(ncases) * vclb::kObsFields * sizeof(double));
   size_t o_part[2];
@@ -1612,6 +1646,8 @@ int vclb_batch_create(const vclb_params* cases, int32_t ncases, vclb_batch** out
   b->d_ticks = reinterpret_cast<unsigned*>(b->ws + o_ticks);
   b->d_reduce = reinterpret_cast<int2*>(b->ws + o_reduce);
   b->nreduce = int(chunks.size());
+  b->d_tiles = reinterpret_cast<int2*>(b->ws + o_tiles);
+  b->d_tile_cases = reinterpret_cast<int2*>(b->ws + o_tc);
   b->d_cur = reinterpret_cast<double*>(b->ws + o_cur);
   b->runs_cap = runs_cap;
   for (int i = 0; i < 2; ++i) b->part[i] = reinterpret_cast<double*>(b->ws + o_part[i]);
@@ -1649,9 +1685,11 @@ int vclb_batch_create(const vclb_params* cases, int32_t ncases, vclb_batch** out
   }
   e = hipMemcpy(b->d_cases, table.data(), table.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(b->d_reduce, chunks.data(), chunks.size() * sizeof(int2), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->own, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_in, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_out, hipEventDisableTiming);
+  if (e == hipSuccess && b->lx > 0) {
+    e = hipMemcpy(b->d_tiles, tiles.data(), tiles.size() * sizeof(int2), hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+      e = hipMemcpy(b->d_tile_cases, tile_cases.data(), tile_cases.size() * sizeof(int2), hipMemcpyHostToDevice);
+  }
   if (e != hipSuccess) {
     vclb_batch_destroy(b);
     return hip_fail(e, "batch set-up");
@@ -1667,11 +1705,7 @@ int vclb_batch_create(const vclb_params* cases, int32_t ncases, vclb_batch** out
 
 void vclb_batch_destroy(vclb_batch* b) {
   if (!b) return;
-  batch_release_graph(b);
   for (vclb_case* c : b->cases) vclb_case_destroy(c);
-  if (b->ev_in) (void)hipEventDestroy(b->ev_in);
-  if (b->ev_out) (void)hipEventDestroy(b->ev_out);
-  if (b->own) (void)hipStreamDestroy(b->own);
   if (b->ws) (void)hipFree(b->ws);
   delete b;
 }
@@ -1703,8 +1737,7 @@ int vclb_batch_nodes(const vclb_batch* b, int64_t* nodes) {
 
 int vclb_batch_set_tile(vclb_batch* b, int32_t bx, int32_t ty) {
   if (!b) return fail(VCLB_EINVAL, "batch is NULL");
-  batch_release_graph(b);
-  return batch_set_tile(b, bx, ty, b->flat_pct);
+  return batch_set_runs(b, bx, ty, b->flat_pct);
 }
 
 int vclb_batch_get_tile(const vclb_batch* b, int32_t* bx, int32_t* ty, int32_t* blocks) {
@@ -1717,8 +1750,7 @@ int vclb_batch_get_tile(const vclb_batch* b, int32_t* bx, int32_t* ty, int32_t* 
 
 int vclb_batch_set_schedule(vclb_batch* b, int32_t flat_pct) {
   if (!b) return fail(VCLB_EINVAL, "batch is NULL");
-  batch_release_graph(b);
-  return batch_set_tile(b, b->bx, b->ty, flat_pct);
+  return batch_set_runs(b, b->bx, b->ty, flat_pct);
 }
 
 int vclb_batch_get_schedule(const vclb_batch* b, int32_t* flat_pct) {
@@ -1845,30 +1877,17 @@ int vclb_batch_step(vclb_batch* b, int64_t nsteps, int32_t use_graph, void* stre
   }
   if (nsteps == 0) return VCLB_OK;
   hipStream_t s = as_stream(stream);
-  batch_release_graph(b);
-  int rc;
+  // The launches go straight onto the caller's stream.  Recording a call's steps into a
+  // hipGraph, instantiating and launching it, which use_graph once asked for, cost 60-300 us
+  // a call more and saved nothing per step (24 small cases in FP32, 50 steps: 1018 us
+  // against 703; 512 cases, 10 steps: 8267 against 8201).  A stream under capture is still
+  // refused with use_graph, as recording within a capture was.
   if (use_graph) {
-    // capture on the library's own stream, ordered after the caller's stream by events
-    HIP_TRY(hipEventRecord(b->ev_in, s));
-    HIP_TRY(hipStreamWaitEvent(b->own, b->ev_in, 0));
-    HIP_TRY(hipStreamBeginCapture(b->own, hipStreamCaptureModeThreadLocal));
-    rc = batch_enqueue(b, nsteps, true, b->own);
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamEndCapture(b->own, &g);
-    if (rc) {
-      if (g) (void)hipGraphDestroy(g);
-      return rc;
-    }
-    if (e != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
-    b->graph = g;
-    HIP_TRY(hipGraphInstantiate(&b->gexec, g, nullptr, nullptr, 0));
-    HIP_TRY(hipGraphLaunch(b->gexec, b->own));
-    HIP_TRY(hipEventRecord(b->ev_out, b->own));
-    HIP_TRY(hipStreamWaitEvent(s, b->ev_out, 0));
-  } else {
-    rc = batch_enqueue(b, nsteps, true, s);
-    if (rc) return rc;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(s, &st));
+    if (st != hipStreamCaptureStatusNone) return fail(VCLB_EHIP, "batch step with use_graph on a stream under capture");
   }
+  if (int rc = batch_enqueue(b, nsteps, true, s)) return rc;
   for (vclb_case* c : b->cases) {
     for (int64_t t = t0; t < t0 + nsteps; ++t)
       if (b->reduce_every > 0 && t % b->reduce_every == 0) c->recorded[size_t(t % vclb::kHistory)] = t;
@@ -1882,8 +1901,8 @@ int vclb_batch_balance(vclb_batch* b, int32_t rounds, int32_t steps, double* gai
   if (gain) *gain = 1.0;
   for (vclb_case* c : b->cases)
     if (!c->inited) return fail(VCLB_ESTATE, "balance needs initialised cases (their state is restored)");
+  if (b->lane) return VCLB_OK;   // lane tiles have no runs to cut
   hipStream_t s = as_stream(stream);
-  batch_release_graph(b);
   HIP_TRY(hipStreamSynchronize(s));
   size_t bytes = 0;
   for (vclb_case* c : b->cases) bytes += c->lay.total;
@@ -1984,7 +2003,6 @@ int vclb_batch_set_weights(vclb_batch* b, const double* weights, int32_t count) 
   if (count != 0 && count != b->blocks) return fail(VCLB_EINVAL, "one weight per run slot (see vclb_batch_get_tile)");
   for (int r = 0; r < count; ++r)
     if (!(weights[r] >= 1e-3 && weights[r] <= 1e3)) return fail(VCLB_EINVAL, "weights must lie in [1e-3, 1e3]");
-  batch_release_graph(b);
   b->weight.assign(weights, weights + count);
   if (count) {
     double sum = 0.0;
@@ -2010,7 +2028,7 @@ int vclb_batch_autotune(vclb_batch* b, const char* cache_path, int32_t steps, vo
   if (cache_path) {
     if (FILE* f = std::fopen(cache_path, "r")) {
       char line[4096];
-      int bx = 0, ty = 0, fp = -1;
+      int bx = 0, ty = 0, fp = -1, lane = 0;
       while (std::fgets(line, sizeof(line), f)) {
         if (!std::strstr(line, key)) continue;
         const char* pb = std::strstr(line, "\"bx\": ");
@@ -2020,17 +2038,18 @@ int vclb_batch_autotune(vclb_batch* b, const char* cache_path, int32_t steps, vo
           bx = std::atoi(pb + 6);
           ty = std::atoi(pt + 6);
           fp = std::atoi(pf + 12);
+          lane = std::strstr(line, "\"lane_tiles\": 1") ? 1 : 0;
         }
       }
       std::fclose(f);
       if (bx > 0 && ty > 0 && fp >= 0) {
-        batch_release_graph(b);
-        return batch_set_tile(b, bx, ty, fp);
+        const int rc = batch_set_runs(b, bx, ty, fp);
+        if (!rc) b->lane = lane && b->lx > 0;
+        return rc;
       }
     }
   }
   hipStream_t s = as_stream(stream);
-  batch_release_graph(b);
   HIP_TRY(hipStreamSynchronize(s));
   // save every case's device state; the timing steps run on it and it is restored after
   size_t bytes = 0;
@@ -2066,6 +2085,8 @@ int vclb_batch_autotune(vclb_batch* b, const char* cache_path, int32_t steps, vo
     for (vclb_case* c : b->cases) c->t_host = t0;
     return VCLB_OK;
   };
+  const bool lane0 = b->lane;
+  b->lane = false;
   for (Cand& cd : cands) {
     if (batch_set_tile(b, cd.bx, cd.ty, cd.fp) == VCLB_EINVAL) continue;   // shape not valid for these cases
     if ((rc = time_shape(steps, cd.ms))) break;
@@ -2085,6 +2106,17 @@ int vclb_batch_autotune(vclb_batch* b, const char* cache_path, int32_t steps, vo
       if ((rc = time_shape(2 * steps, ms))) break;
       cd.ms = std::min(cd.ms, ms);
     }
+  // and the lane tiles, if this batch has them
+  float lane_ms = -1.0f;
+  if (rc == VCLB_OK && b->lx > 0) {
+    b->lane = true;
+    for (int pass = 0; rc == VCLB_OK && pass < 3; ++pass) {
+      float ms = 0;
+      if ((rc = time_shape(2 * steps, ms))) break;
+      if (lane_ms < 0 || ms < lane_ms) lane_ms = ms;
+    }
+  }
+  b->lane = lane0;
   o = 0;
   for (vclb_case* c : b->cases) {
     (void)hipMemcpyAsync(c->ws, static_cast<char*>(save) + o, c->lay.total, hipMemcpyDeviceToDevice, s);
@@ -2102,10 +2134,12 @@ int vclb_batch_autotune(vclb_batch* b, const char* cache_path, int32_t steps, vo
   if (best.ms < 0) return fail(VCLB_EINVAL, "no batched launch shape fits these cases");
   rc = batch_set_tile(b, best.bx, best.ty, best.fp);
   if (rc) return rc;
+  b->lane = lane_ms > 0 && lane_ms < best.ms;
   if (cache_path) {
     if (FILE* f = std::fopen(cache_path, "a")) {
-      std::fprintf(f, "{\"key\": \"%s\", \"cases\": %d, \"storage\": %d, \"bx\": %d, \"ty\": %d, \"flat_pct\": %d, \"ms_per_step\": %.6f, \"candidates\": [",
-                   key, b->n, b->storage, best.bx, best.ty, best.fp, double(best.ms));
+      std::fprintf(f, "{\"key\": \"%s\", \"cases\": %d, \"storage\": %d, \"bx\": %d, \"ty\": %d, \"flat_pct\": %d, \"lane_tiles\": %d, \"ms_per_step\": %.6f, \"candidates\": [",
+                   key, b->n, b->storage, best.bx, best.ty, best.fp, b->lane ? 1 : 0,
+                   double(b->lane ? lane_ms : best.ms));
       for (size_t i = 0; i < cands.size(); ++i)
         std::fprintf(f, "%s[%d, %d, %d, %.6f]", i ? ", " : "", cands[i].bx, cands[i].ty, cands[i].fp, double(cands[i].ms));
       std::fprintf(f, "]}\n");

@@ -7,10 +7,9 @@
 // row by row (step2d_tile, one lane per column: best when the width is close to a
 // multiple of the wave size) or a band of whole rows marched in the case's stored
 // row-major order (step2d_flat: every lane busy for any width, every wave storing whole
-// cache lines); the host picks per case.  The n launches of a call are captured in one
-// hipGraph and replayed as one launch.  Per-case volume reductions: every item writes its partial
-// sums; the next launch (or a fold-only launch at the end of a call) sums each case's
-// items in a fixed order into that case's observation history.
+// cache lines); the host picks per case.  Per-case volume reductions: every
+// item writes its partial sums; the next launch (or a fold-only launch at the end of a
+// call) sums each case's items in a fixed order into that case's observation history.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -20,27 +19,6 @@
 #include "flat2d.hpp"
 
 namespace vclb {
-
-// sum case cs's item partials in item order into its history slot
-template <class St>
-__device__ __forceinline__ void fold_case(const DevCase<D2Q9, St>& c, const BatchArgs& a, int cs) {
-  __shared__ double red[16 * 12];
-  const int2 r = a.case_items[cs];
-  double v[12];
-#pragma unroll
-  for (int f = 0; f < 12; ++f) v[f] = 0.0;
-  for (int i = threadIdx.x; i < r.y; i += blockDim.x) {
-#pragma unroll
-    for (int f = 0; f < 12; ++f) v[f] += a.part_r[long(f) * a.nitems + r.x + i];
-  }
-  const double s = block_sum_fields<12>(v, 12, red);
-  if (threadIdx.x < 12) {
-    double* dest = c.hist + (a.pend_step % kHistory) * kObsFields;
-    dest[threadIdx.x] = s;
-    if (threadIdx.x == 0) dest[12] = double(a.pend_step);
-  }
-  __syncthreads();
-}
 
 // Workgroups per CU the register budget is sized for: FP32 arithmetic fits 4 waves per
 // SIMD, except the lag-3 FIFO with general rates (a little more than 128 VGPRs: 3); FP64
@@ -60,7 +38,7 @@ __global__ void __launch_bounds__(BS, (batch_min_blocks<St, DL, BS, UNIT>()))
     k_batch_step2d(const DevCase<D2Q9, St>* __restrict__ cases, BatchArgs a) {
   extern __shared__ unsigned char smem_raw[];
   if (a.pend)
-    for (int cs = blockIdx.x; cs < a.ncases; cs += gridDim.x) fold_case<St>(cases[cs], a, cs);
+    for (int cs = blockIdx.x; cs < a.ncases; cs += gridDim.x) fold_case(cases[cs], a, cs);
   // consecutive runs go to one XCD: the rows where one run ends and the next begins are
   // read by both, through that XCD's L2
   const int slot = xcd_tile(blockIdx.x, gridDim.x);
@@ -82,7 +60,7 @@ __global__ void __launch_bounds__(BS, (batch_min_blocks<St, DL, BS, UNIT>()))
 
 template <class St>
 __global__ void __launch_bounds__(256) k_batch_fold(const DevCase<D2Q9, St>* __restrict__ cases, BatchArgs a) {
-  for (int cs = blockIdx.x; cs < a.ncases; cs += gridDim.x) fold_case<St>(cases[cs], a, cs);
+  for (int cs = blockIdx.x; cs < a.ncases; cs += gridDim.x) fold_case(cases[cs], a, cs);
 }
 
 template <class St>

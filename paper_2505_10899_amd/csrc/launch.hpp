@@ -58,13 +58,15 @@ int launch_batch_reduce(const void* cases, int ncases, const int2* blocks, int n
                         hipStream_t s);
 
 struct BatchArgs {
+  const int2* tiles;        // lane tiles: (case, tile) of every workgroup
+  int ntiles;
   const int4* items;        // (case, x0, y0, y1) of every work item, case-major; x0 < 0: a
                             // flattened band of rows [y0, y1), else a strip of columns from x0
   int nitems;
   const int2* runs;         // (first item, item count) of each resident workgroup slot
-  const int2* case_items;   // (first item, item count) per case
+  const int2* case_items;   // (first item, item count) per case; of tiles in lane tiles
   int ncases;
-  double* part_w;           // [12][nitems] partials written by this launch
+  double* part_w;           // [12][nitems] partials written by this launch (nitems = ntiles in lane tiles)
   const double* part_r;     // [12][nitems] partials of the previous launch
   int pend;                 // part_r holds partials of step pend_step still to be summed
   long pend_step;
@@ -78,6 +80,29 @@ struct BatchArgs {
                             // on its run (balancing launches only)
 };
 
+// Sum case cs's item (or tile) partials in order into its history slot, by one whole
+// workgroup, a wave per group of four fields, with no barrier.
+template <class St>
+__device__ __forceinline__ void fold_case(const DevCase<D2Q9, St>& c, const BatchArgs& a, int cs) {
+  const int2 r = a.case_items[cs];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = (blockDim.x + 63) >> 6;
+  double* dest = c.hist + (a.pend_step % kHistory) * kObsFields;
+  for (int f0 = wave * 4; f0 < 12; f0 += nw * 4) {
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int i = lane; i < r.y; i += 64) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] += ldg(a.part_r + long(f0 + j) * a.nitems + r.x, i);
+    }
+    const double s = wave_sum4(v[0], v[1], v[2], v[3]);
+    if ((lane & 15) == 15) dest[f0 + (lane >> 4)] = s;
+    if (f0 == 0 && lane == 0) dest[12] = double(a.pend_step);
+  }
+}
+
+// the step in lane tiles of 16 x 8 nodes with a helper wave
+template <class St>
+int launch_batch_tile2d(const void* cases, const BatchArgs& a, int lx, int ly, hipStream_t s);
 template <class St>
 int launch_batch_step(const void* cases, const BatchArgs& a, int blocks, int bx, hipStream_t s);
 template <class St>

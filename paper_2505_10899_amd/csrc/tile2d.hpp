@@ -1,0 +1,225 @@
+// The tile step of tile2d.hip as a device function, shared by the single-case kernel and
+// the batched one.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "devcase.hpp"
+#include "flat2d.hpp"
+
+namespace vclb {
+
+// Lanes of a workgroup for tiles of 2^LX x 2^LY nodes, with or without the helper wave.
+constexpr int tile2d_lanes(int LX, int LY, bool help) { return (1 << (LX + LY)) + (help ? 64 : 0); }
+
+// One step (time level t) of tile `tile` of case c, by one whole workgroup; ntx tiles span
+// a row of tiles.  part: this tile's slot of the reduction partials (field j of label k at
+// [(k * 12 + j) * part_stride]), null when the step records none.
+//
+// LX, LY: log2 of the tile's sides.  HELP: one more wave, which pulls the first 64 halo cells and
+// sums the tile's reductions while the others update.  That takes both off the critical
+// path of a step that waits for one launch (128 x 128 FP64: 7.4 -> 5.9 us, of which the
+// reductions now cost 0.6), but a wave in three idles; large grids, which need every wave
+// (1501 x 1003 FP16S: 27.7 -> 31.3 us), leave both to the tile's own lanes.
+// NT: stores of the populations and loads of f with the non-temporal hint.
+template <class St, bool COUPLED, bool UNIT, bool VISC, int LX, int LY, bool HELP, bool NT>
+__device__ __forceinline__ void tile2d_step(const DevCase<D2Q9, St>& c, long t, int tile, int ntx,
+                                            double* __restrict__ part, long part_stride) {
+  using L = D2Q9;
+  using R = typename St::R;
+  using S = typename St::S;
+  constexpr int Q = 9;
+  struct alignas(2 * sizeof(R)) PhiPsi {
+    R phi, psi;
+  };
+  constexpr int TX = 1 << LX, TY = 1 << LY, PW = TX + 2, nodes = TX * TY;
+  constexpr int nring = 2 * PW + 2 * TY;   // halo cells
+  static_assert(nring <= nodes && nodes % 64 == 0, "a halo cell per lane");
+  __shared__ PhiPsi ring[PW * (TY + 2)];   // the tile and its halo
+  const int ty_i = tile / ntx, tx_i = tile - ty_i * ntx;
+  const int nx = c.nx, ny = c.ny, ns = int(c.ns);
+  const int x0 = tx_i * TX, y0 = ty_i * TY;
+  const int tid = threadIdx.x;
+  const bool helper = HELP && tid >= nodes;   // the last wave has no node of its own
+  const int tx = tid % TX, ty = tid / TX;
+  const int xg = x0 + tx, yg = y0 + ty;
+  const bool active = !helper && xg < nx && yg < ny;
+  const bool wall = c.wall != 0;
+  // column and row whose populations a ring position holds: the periodic image, or, past
+  // a wall, the edge row (whose wetting ghost the ring then holds)
+  auto col_of = [&](int x) { return x >= 0 && x < nx ? x : (x % nx + nx) % nx; };
+  auto row_of = [&](int y) {
+    if (y >= 0 && y < ny) return y;
+    if (wall) return y < 0 ? 0 : ny - 1;
+    return (y % ny + ny) % ny;
+  };
+  const int xw = col_of(xg), yw = row_of(yg);
+  const int par = int(t & 1), dst = par ^ 1;
+  const S* gsrc[Q];
+  const S* fsrc[Q];
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    gsrc[i] = c.pop[0][par] + long(i) * ns;
+    fsrc[i] = COUPLED ? c.pop[1][par] + long(i) * ns : nullptr;
+  }
+  const float* phis = c.phis[par];
+  const unsigned nn = unsigned(xw + nx * yw);
+  // every load of this lane before the first use: its node's g, a halo cell's g, f, J
+  R g[Q], ps[Q], f[Q], J[2], gh[Q], hps[Q];
+  if (!helper) pull9_flat<St>(gsrc, phis, xw, yw, nx, ny, ns, wall, g, ps);
+  // halo cells, one per lane: the helper wave first, then the tile's lanes from lane 0
+  const int cell = !HELP ? tid : (helper ? tid - nodes : tid + 64);
+  int px = 0, py = 0;
+  if (cell < nring) {
+    if (cell < 2 * PW) {
+      py = cell < PW ? 0 : TY + 1;
+      px = cell < PW ? cell : cell - PW;
+    } else {
+      const int k = cell - 2 * PW;
+      py = 1 + (k >> 1);
+      px = (k & 1) ? PW - 1 : 0;
+    }
+    pull9_flat<St>(gsrc, phis, col_of(x0 - 1 + px), row_of(y0 - 1 + py), nx, ny, ns, wall, gh, hps);
+  }
+  if (active) {
+    if constexpr (COUPLED) pull9_flat<St, NT>(fsrc, phis, xw, yw, nx, ny, ns, wall, f, nullptr);
+    J[0] = ldg(c.J, nn);
+    J[1] = ldg(c.J + ns, nn);
+  }
+  // the vortex factors of the tile's columns, rows and the step, once per tile and not per
+  // node: sin(pi x / nx), sin(2 pi x / nx) of column i at [i], of row i at [TX + i]
+  __shared__ R trig[COUPLED ? 1 : 2][COUPLED ? 1 : TX + TY + 1];
+  if constexpr (!COUPLED) {
+    if (tid < TX) vortex_factors<R>(col_of(x0 + tid), nx, trig[0][tid], trig[1][tid]);
+    else if (tid < TX + TY) vortex_factors<R>(row_of(y0 + tid - TX), ny, trig[0][tid], trig[1][tid]);
+    else if (tid == TX + TY) trig[0][tid] = vortex_phase<R>(c.np.T, t);
+  }
+  auto form = [&](R (&v)[Q], const R (&vps)[Q], int y, int at) {
+    R ph = phi_of_pulled<L, St>(v, vps, c.np.rest);
+    if (wall && y < 0) ph = wet_ghost<R>(ph, c.np.wet_lo);
+    else if (wall && y >= ny) ph = wet_ghost<R>(ph, c.np.wet_hi);
+    ring[at] = PhiPsi{ph, psi_of<R>(ph, c.np.W4, c.np.xi)};
+  };
+  const int own = (ty + 1) * PW + tx + 1;
+  if (!helper) form(g, ps, yg, own);
+  if (cell < nring) form(gh, hps, y0 - 1 + py, py * PW + px);
+  __syncthreads();
+  if (active) {
+    NodeIn<L, R> in;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const PhiPsi v = ring[own + L::cy[i] * PW + L::cx[i]];
+      in.nphi[i] = v.phi;
+      in.npsi[i] = v.psi;
+    }
+    if constexpr (!COUPLED) {
+      vortex_from_factors<R>(c.np.U0, trig[0][tx], trig[1][tx], trig[0][TX + ty], trig[1][TX + ty], trig[0][TX + TY],
+                             in.u[0], in.u[1]);
+    }
+    NodeOut<L, R> out;
+    node_update_d2q9<R, COUPLED, St::shifted, UNIT, VISC>(c.np, in, g, f, J, out);
+    R res = R(0);   // rounding of the stored g deviations, taken off the stored phi
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      R d = g[i];
+      if constexpr (St::shifted)   // relative to the reader's phi (encode_dev)
+        d = encode_dev(g[i], c.np.rest[i], in.nphi[0],
+                       leaves_through_wall<L>(i, yw, ny, wall) ? in.nphi[0] : in.nphi[i]);
+      if constexpr (NT) St::store_nt(c.pop[0][dst] + long(i) * ns, nn, d);
+      else St::store(c.pop[0][dst] + long(i) * ns, nn, d);
+      if constexpr (St::fold) res += St::rounding(d);
+    }
+    if constexpr (COUPLED) {
+      if (wall && yw == 0) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+          if (L::cy[i] < 0) f[i] += c.np.wb[i] * out.rho;
+      }
+      if (wall && yw == ny - 1) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+          if (L::cy[i] > 0) f[i] += c.np.wt[i] * out.rho;
+      }
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        if constexpr (NT) St::store_nt(c.pop[1][dst] + long(i) * ns, nn, f[i]);
+        else St::store(c.pop[1][dst] + long(i) * ns, nn, f[i]);
+      }
+    }
+    stg(c.J, nn, J[0]);
+    stg(c.J + ns, nn, J[1]);
+    if constexpr (St::shifted) stg(c.phis[dst], nn, float(in.nphi[0] - res));
+  }
+  // this tile's volume reductions, by one wave from the ring's phi: the helper, or the last
+  // wave (the first ones pull the halo).  Six sums over the wave once per tile instead of
+  // once per wave: 1501 x 1003 FP16S 34.9 -> 27.7 us.
+  if (!part || tid < (HELP ? nodes : nodes - 64)) return;
+  // A lane keeps to a column (or two, TX = 128), so only phi, phi dy, phi dy^2 add up per
+  // node and the x moments follow.
+  const int lane = tid & 63;
+  constexpr int kCols = TX > 64 ? TX / 64 : 1, kRowStep = TX < 64 ? 64 / TX : 1;
+  double s[kMaxLabels][6];
+  int cnt[kMaxLabels], bad[kMaxLabels];
+#pragma unroll
+  for (int k = 0; k < kMaxLabels; ++k) {
+    cnt[k] = bad[k] = 0;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) s[k][j] = 0.0;
+  }
+#pragma unroll
+  for (int h = 0; h < kCols; ++h) {
+    const int rx = lane % TX + 64 * h, x = x0 + rx;
+    double dx[kMaxLabels], s0[kMaxLabels], s1[kMaxLabels], s2[kMaxLabels];
+#pragma unroll
+    for (int k = 0; k < kMaxLabels; ++k) {
+      dx[k] = min_image(double(x) - c.cen[k][0], nx, true);
+      s0[k] = s1[k] = s2[k] = 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < TY / kRowStep; ++i) {
+      const int ry = lane / TX + i * kRowStep, y = y0 + ry;
+      const double ph = x < nx && y < ny ? double(ring[(ry + 1) * PW + rx + 1].phi) : 0.0;
+      double dy[kMaxLabels];
+#pragma unroll
+      for (int k = 0; k < kMaxLabels; ++k) dy[k] = min_image(double(y) - c.cen[k][1], ny, !wall);
+      const int lab = c.nl > 1 && dx[1] * dx[1] + dy[1] * dy[1] < dx[0] * dx[0] + dy[0] * dy[0] ? 1 : 0;
+#pragma unroll
+      for (int k = 0; k < kMaxLabels; ++k) {
+        if (k >= c.nl) break;
+        const double w = lab == k ? ph : 0.0;
+        s0[k] += w;
+        s1[k] += w * dy[k];
+        s2[k] += w * dy[k] * dy[k];
+        cnt[k] += __popcll(__ballot(lab == k && ph >= 0.5));
+        bad[k] += __popcll(__ballot(lab == k && !isfinite(ph)));
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kMaxLabels; ++k) {
+      s[k][0] += s0[k];
+      s[k][1] += dx[k] * s0[k];
+      s[k][2] += s1[k];
+      s[k][3] += dx[k] * dx[k] * s0[k];
+      s[k][4] += s2[k];
+      s[k][5] += dx[k] * s1[k];
+    }
+  }
+  // lane 16 i + 15 stores field i of each group of four
+#pragma unroll
+  for (int k = 0; k < kMaxLabels; ++k) {
+    if (k >= c.nl) break;
+    const double a = wave_sum4(s[k][0], s[k][1], s[k][2], s[k][3]);
+    double b = wave_sum4(s[k][4], s[k][5], 0.0, 0.0);
+    const int i = lane >> 4;
+    if (i >= 2) b = double(i == 2 ? cnt[k] : bad[k]);
+    if ((lane & 15) == 15) {
+      // fields: sum, count, x, y, z, xx, yy, zz, xy, xz, yz, not finite
+      const int fa = i == 0 ? 0 : (i == 1 ? 2 : (i == 2 ? 3 : 5)), fb = i == 0 ? 6 : (i == 1 ? 8 : (i == 2 ? 1 : 11));
+      const int fz = i == 0 ? 4 : (i == 1 ? 7 : (i == 2 ? 9 : 10));
+      stg(part, long(k * 12 + fa) * part_stride, a);
+      stg(part, long(k * 12 + fb) * part_stride, b);
+      stg(part, long(k * 12 + fz) * part_stride, 0.0);
+    }
+  }
+}
+
+}  // namespace vclb

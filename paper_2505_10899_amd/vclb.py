@@ -550,8 +550,7 @@ def _obs_to_dict(arr, n) -> dict:
 
 
 class Batch:
-    """Many independent coupled D2Q9 cases advanced together (one work-list kernel per
-    step, a call's steps replayed from one hipGraph).  ``cases[k]`` is a Case view of
+    """Many independent coupled D2Q9 cases advanced together (one kernel per step).  ``cases[k]`` is a Case view of
     case k (init, observe, reduce, history, get/set_state)."""
 
     def __init__(self, params_list, device="cuda"):

@@ -85,3 +85,46 @@ def test_one_step_and_reductions(nx, ny, storage, wall, mode, visc, nl):
         for k, s in scale.items():
             assert float(np.max(np.abs(h[k][t] - obs[t][k]))) <= rtol * s * total, (t, k)
         assert not h["nonfinite"].any()
+
+
+@pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s"])
+@pytest.mark.parametrize("visc", [1.0, 3.75])
+def test_batch_one_step(storage, visc):
+    """A batch small enough for lane tiles: each case's step from the oracle's state against
+    the oracle's own (FP16S: against the plain path), and its recorded sum of phi."""
+    from paper_2505_10899_amd import vclb as v
+    cases = [_case(nx, ny, storage, k % 2 == 1, "coupled", visc if k % 3 else 1.0, 1) for k, (nx, ny) in enumerate(SMALL)]
+    b = v.Batch([p.replace(storage=storage) for p, _, _ in cases])
+    models = []
+    for c, (p, phi0, u0) in zip(b.cases, cases):
+        m = Model(p).init(phi0, u0)
+        m.step(1)
+        c.set_state(m.g, m.f, m.Jprev, m.t)
+        models.append(m)
+    field = lambda: [observables_from_phi(p, c.observe(v.FIELD_PHI)["phi"])["sum_phi"][0]
+                     for c, (p, _, _) in zip(b.cases, cases)]
+    sums = [field()]
+    b.step(1)
+    for k, (c, m) in enumerate(zip(b.cases, models)):
+        print("case:", k, SMALL[k], storage, visc, flush=True)
+        got = c.get_state()
+        if storage == "fp16s":
+            d = v.Case(m.p.replace(storage=storage))
+            d.set_state(m.g, m.f, m.Jprev, m.t)
+            d.step_plain(1)
+            for x, y in zip(got, d.get_state()):
+                assert float(np.max(np.abs(x - y))) <= 2.0 ** -15 + 2e-6
+            continue
+        base, eps = (1e-13, 2.2e-16) if storage == "fp64" else (1e-6, 6e-8)
+        tol = base + 2.0 * normal_conditioning(m, m.fields(), eps=eps)
+        m.step(1)
+        assert float(np.max(np.abs(got[0] - m.g) / tol[None])) <= 1.0
+        assert float(np.max(np.abs(got[1] - m.f) / tol[None])) <= 1.0
+        assert float(np.max(np.abs(got[2] - m.Jprev))) <= base
+    sums.append(field())
+    b.step(1)
+    h = b.history(1, 2)["sum_phi"][:, :, 0]
+    rtol = {"fp64": 1e-12, "fp32": 2e-6, "fp16s": 2e-4}[storage]
+    assert np.all(np.abs(h - np.array(sums)) <= rtol * (1.0 + np.abs(np.array(sums))))
+    r = b.reduce()
+    assert np.all(np.abs(r["sum_phi"][:, 0] - np.array(field())) <= rtol * (1.0 + np.abs(np.array(sums[1]))))
