@@ -401,6 +401,19 @@ void tile2d_choose(const vclb_params& p, vclb::Tile& t) {
   if (tile2d_fits(p, u)) t = u;
 }
 
+// Whether a 3D case steps in two passes in stored order (flat3d.hip) or as a section march.
+// The march wins where its sections and rows fit: from 2^21 nodes on, rows that start on
+// cache lines, 4- or 8-byte storage (96 x 96 x 384 FP32 263 / 296 us a step, FP64 505 / 566;
+// 64 x 64 x 300 FP32 115 / 102).  FP16S moves few enough bytes that the second reading of g
+// costs little (96 x 96 x 384 200 / 202, 128 x 128 x 200 240 / 184).  Beyond 2^28 nodes the
+// 32-bit byte offsets of the pairs end (16 bytes in FP64).
+bool flat3d_chosen(const vclb_params& p) {
+  const long n = long(p.nx) * p.ny * p.nz;
+  if (n > (1L << 28) - 1) return false;
+  const bool lines = size_t(p.nx) * storage_bytes(p.storage) % 128 == 0;
+  return !(p.storage != VCLB_FP16S && lines && n >= (1L << 21));
+}
+
 vclb::Tile default_tile(const vclb_params& p, int ncu, bool wide_ok = true) {
   vclb::Tile t;
   if (p.lattice == VCLB_D2Q9) {
@@ -432,13 +445,20 @@ vclb::Tile default_tile(const vclb_params& p, int ncu, bool wide_ok = true) {
     // longer segments of two per CU measured faster (fewer halo planes per segment).
     // With 4-byte arithmetic and at least 96 columns in x, one 96 x 8 section of 768
     // lanes per CU instead (measured 4.6% faster in FP32 and 15% in FP16S on 96 x 96 x 384).
+    // (or 128 x 6 where that leaves fewer lanes idle)
     const bool wide = wide_ok && p.storage != VCLB_FP64 && p.nx >= 96;
+    auto padded = [&](int bx, int by) { return long((p.nx + bx - 1) / bx * bx) * ((p.ny + by - 1) / by * by); };
     t.bx = wide ? 96 : 32;
     t.by3 = 8;
-    const long cols = long((p.nx + t.bx - 1) / t.bx) * ((p.ny + 7) / 8);
+    if (wide && padded(128, 6) < padded(96, 8)) {
+      t.bx = 128;
+      t.by3 = 6;
+    }
+    const long cols = long((p.nx + t.bx - 1) / t.bx) * ((p.ny + t.by3 - 1) / t.by3);
     const long per_cu = wide ? 1 : (p.storage == VCLB_FP16S ? 3 : 2);
     const long segs = std::max(1L, per_cu * ncu / cols);
     t.ty = int(std::max(8L, std::min(64L, (p.nz + segs - 1) / segs)));
+    t.flat = flat3d_chosen(p);
   }
   return t;
 }
@@ -813,6 +833,7 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
     if (FILE* f = std::fopen(cache_path, "r")) {
       char line[4096];
       int bx = 0, ty = 0, by3 = 0, lx = 0, ly = 0;
+      bool flat = false;
       while (std::fgets(line, sizeof(line), f)) {
         if (!std::strstr(line, key)) continue;
         const char* pb = std::strstr(line, "\"bx\": ");
@@ -825,6 +846,7 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
           // "lane_tile": log2 of the sides of a tile of one lane per node (absent: a march)
           const char* pl = std::strstr(line, "\"lane_tile\": [");
           if (!pl || std::sscanf(pl + 14, "%d, %d", &lx, &ly) != 2) lx = ly = 0;
+          flat = std::strstr(line, "\"flat\": 1") != nullptr;   // the two-pass 3D step
         }
       }
       std::fclose(f);
@@ -836,6 +858,7 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
         if (!rc && p.lattice == VCLB_D2Q9 && vclb::tile2d_shape_ok(lx, ly) && long(p.nx) * p.ny <= (1L << 26) &&
             tile2d_fits(p, t))
           c->tile = t;
+        if (!rc && flat && p.lattice == VCLB_D3Q19 && default_tile(p, 256).flat) c->tile.flat = true;
         return rc;
       }
     }
@@ -863,6 +886,11 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       ncu = 256;
     const int shapes[][2] = {{32, 8}, {64, 4}, {16, 16}, {32, 4}, {64, 2}, {16, 8}, {96, 8}, {48, 16}, {64, 12}};
+    if (default_tile(p, 256).flat) {
+      vclb::Tile t = c->tile;
+      t.flat = true;
+      cands.push_back(t);
+    }
     for (const auto& sh : shapes)
       for (int per_cu : {1, 2, 3, 4}) {
         if (sh[0] * sh[1] > 256 && (p.storage == VCLB_FP64 || per_cu > 1)) continue;   // wide: one per CU
@@ -871,7 +899,7 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
         const int ty = int(std::max(1L, (p.nz + segs - 1) / segs));
         vclb::Tile t{sh[0], ty, sh[1]};
         bool dup = false;
-        for (const vclb::Tile& u : cands) dup = dup || (u.bx == t.bx && u.ty == t.ty && u.by3 == t.by3);
+        for (const vclb::Tile& u : cands) dup = dup || (!u.flat && u.bx == t.bx && u.ty == t.ty && u.by3 == t.by3);
         if (!dup) cands.push_back(t);
       }
   }
@@ -924,8 +952,8 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
   if (cache_path) {
     if (FILE* f = std::fopen(cache_path, "a")) {
       const vclb::Tile& b = c->tile;
-      std::fprintf(f, "{\"key\": \"%s\", \"shape\": \"%s\", \"bx\": %d, \"ty\": %d, \"by3\": %d, \"lane_tile\": [%d, %d], \"ms_per_step\": %.6f, \"candidates\": [",
-                   key, desc.c_str(), b.bx, b.ty, b.by3, b.lx, b.ly, double(ms[size_t(best)]));
+      std::fprintf(f, "{\"key\": \"%s\", \"shape\": \"%s\", \"bx\": %d, \"ty\": %d, \"by3\": %d, \"lane_tile\": [%d, %d], \"flat\": %d, \"ms_per_step\": %.6f, \"candidates\": [",
+                   key, desc.c_str(), b.bx, b.ty, b.by3, b.lx, b.ly, b.flat ? 1 : 0, double(ms[size_t(best)]));
       for (size_t i = 0; i < cands.size(); ++i)
         std::fprintf(f, "%s[%d, %d, %d, %.6f]", i ? ", " : "", cands[i].bx, cands[i].ty, cands[i].by3, double(ms[i]));
       std::fprintf(f, "]}\n");

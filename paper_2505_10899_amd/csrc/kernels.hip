@@ -473,7 +473,7 @@ int launch_step_fused(const DevCase<L, St>& c, const Tile& tile, int reduce, hip
     if (bad_shape) return -1;
     return hipGetLastError() == hipSuccess ? 0 : -3;
   } else {
-    return launch_step3d<St>(c, tile, reduce, s);
+    return tile.flat ? launch_flat3d<St>(c, reduce, s) : launch_step3d<St>(c, tile, reduce, s);
   }
 }
 

@@ -13,9 +13,11 @@ struct Tile {
   int ty = 32;
   int by3 = 4;
   // D2Q9: with lx > 0 the step runs one lane per node in tiles of 2^lx x 2^ly nodes
-  // (tile2d.hip) and bx, ty are only what a march would use
+  // (tile2d.hip); D3Q19: with flat set, in two passes in stored order (flat3d.hip).  bx, ty
+  // and by3 are then only what a march would use.
   int lx = 0;
   int ly = 0;
+  bool flat = false;
 };
 
 template <class L, class St, bool COUPLED>
@@ -48,6 +50,11 @@ template <class L, class St>
 int launch_finalize(const DevCase<L, St>& c, hipStream_t s);
 template <class St>
 int launch_step3d(const DevCase<D3Q19, St>& c, const Tile& tile, int reduce, hipStream_t s);
+// the two-pass 3D step (flat3d.hip); its first pass sums the reductions of chunks of this
+// many nodes: one per lane on small grids, where four in turn would leave CUs idle
+template <class St>
+int launch_flat3d(const DevCase<D3Q19, St>& c, int reduce, hipStream_t s);
+inline long flat3d_chunk(long n) { return n <= (1L << 19) ? 256 : 1024; }
 template <class St>
 size_t step3d_lds_bytes(int bx, int by3);   // LDS of the fused 3D step for a bx x by3 section
 
@@ -140,6 +147,10 @@ inline int flat_ring_cap(int nx, int B, int lag) {
 // number of workgroups the fused step launches for a case of this shape
 inline long fused_blocks(int dim, int nx, int ny, int nz, const Tile& t) {
   if (dim == 2 && t.lx > 0) return long((nx + (1 << t.lx) - 1) >> t.lx) * ((ny + (1 << t.ly) - 1) >> t.ly);
+  if (dim == 3 && t.flat) {
+    const long n = long(nx) * ny * nz, ch = flat3d_chunk(n);
+    return (n + ch - 1) / ch;
+  }
   if (dim == 2) return long((nx + t.bx - 1) / t.bx) * ((ny + t.ty - 1) / t.ty);
   return long((nx + t.bx - 1) / t.bx) * ((ny + t.by3 - 1) / t.by3) * ((nz + t.ty - 1) / t.ty);
 }
