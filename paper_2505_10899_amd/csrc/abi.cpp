@@ -11,7 +11,9 @@
 #include <cstdint>
 #include <cstring>
 #include <new>
+#include <functional>
 #include <string>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -270,7 +272,7 @@ vclb::DevCase<L, St> make_dev(const vclb_case& c) {
   for (int s = 0; s < 2; ++s)
     for (int b = 0; b < 2; ++b)
       d.pop[s][b] = c.lay.pop[s][b] == SIZE_MAX ? nullptr : reinterpret_cast<S*>(c.ws + c.lay.pop[s][b]);
-  d.J = reinterpret_cast<R*>(c.ws + c.lay.J);
+  d.J = d.Jw = reinterpret_cast<R*>(c.ws + c.lay.J);
   for (int b = 0; b < 2; ++b)
     d.phis[b] = c.lay.phis[b] == SIZE_MAX ? nullptr : reinterpret_cast<float*>(c.ws + c.lay.phis[b]);
   d.t = long(c.t_host);
@@ -782,7 +784,10 @@ int vclb_case_get_state(vclb_case* c, double* g, double* f, double* J, int ptr_k
   return VCLB_OK;
 }
 
-static int do_steps(vclb_case* c, int64_t nsteps, void* stream, bool fused) {
+// place(t): where the state of step t lives if not in the case's own buffers (FP64 D2Q9
+// states of the adjoint's store: g, f and J planes in turn), else null
+static int do_steps(vclb_case* c, int64_t nsteps, void* stream, bool fused,
+                    const std::function<double*(int64_t)>& place = nullptr) {
   if (!c) return fail(VCLB_EINVAL, "case is NULL");
   if (c->p.mass_fix > 0) fused = false;   // the global correction runs on the plain path
   if (nsteps < 0) return fail(VCLB_EINVAL, "nsteps < 0");
@@ -803,6 +808,21 @@ static int do_steps(vclb_case* c, int64_t nsteps, void* stream, bool fused) {
       using L = typename DevTraits<DC>::L;
       using St = typename DevTraits<DC>::St;
       constexpr bool C = decltype(coupled)::value;
+      if constexpr (std::is_same<DC, vclb::DevCase<vclb::D2Q9, vclb::StoreF64>>::value) {
+        if (place) {
+          const int par = int(t & 1);
+          if (double* m = place(t)) {
+            dc.pop[0][par] = m;
+            dc.pop[1][par] = m + 9 * dc.ns;
+            dc.J = m + 18 * dc.ns;
+          }
+          if (double* m = place(t + 1)) {
+            dc.pop[0][par ^ 1] = m;
+            dc.pop[1][par ^ 1] = m + 9 * dc.ns;
+            dc.Jw = m + 18 * dc.ns;
+          }
+        }
+      }
       return fused ? vclb::launch_step_fused<L, St, C>(dc, c->tile, reduce, s)
                    : vclb::launch_step_plain<L, St, C>(dc, reduce, s);
     });
@@ -2190,9 +2210,9 @@ struct AdjStore {
   int64_t nckpt = 0;
   bool has_u0 = false;
   size_t n = 0, state = 0;   // nodes, doubles per state
-  size_t phi0 = 0, u0 = 0, ckpt = 0, seg = 0, lg[2]{}, lf[2]{}, lJ[2]{}, lphi = 0, aux = 0, part = 0,
+  size_t phi0 = 0, u0 = 0, ckpt = 0, seg = 0, lg[2]{}, lf[2]{}, lJ[2]{}, lphi = 0, aux[2]{}, part = 0,
          seed = 0, out = 0, dphi = 0, total = 0;
-  long blocks = 0;
+  long slots = 0;   // of the parameter sums
 };
 
 namespace {
@@ -2216,7 +2236,7 @@ AdjStore adj_layout(const vclb_params& p, int64_t nsteps, int32_t every) {
   a.nckpt = nsteps > 0 ? (nsteps + every - 1) / every : 0;
   a.n = size_t(p.nx) * p.ny;
   a.state = 20 * size_t(vclb::plane_stride(long(a.n)));   // g, f, J in the case's padded planes
-  a.blocks = vclb::adj_blocks(long(a.n));
+  a.slots = vclb::adj_part_slots(p.nx, p.ny);
   size_t off = 0;
   auto take = [&](size_t doubles) {
     const size_t o = off;
@@ -2233,8 +2253,8 @@ AdjStore adj_layout(const vclb_params& p, int64_t nsteps, int32_t every) {
     a.lJ[b] = take(2 * a.n);
   }
   a.lphi = take(a.n);
-  a.aux = take(6 * a.n);
-  a.part = take(2 * size_t(a.blocks));
+  for (int b = 0; b < 2; ++b) a.aux[b] = take(7 * a.n);
+  a.part = take(2 * size_t(a.slots));
   a.seed = take(size_t(vclb::kMaxLabels) * vclb::kSeedFields);
   a.out = take(2);
   a.dphi = take(a.n);
@@ -2358,13 +2378,17 @@ int vclb_adjoint_record(vclb_case* c, const double* phi0, const double* u0, int 
     adj_release(c);
     return rc;
   }
-  for (int64_t k = 0; k < a.nckpt; ++k) {
-    rc = adj_save_state(c, reinterpret_cast<double*>(a.mem + a.ckpt) + size_t(k) * a.state, s);
-    if (!rc) rc = vclb_step(c, std::min<int64_t>(a.every, a.nsteps - k * a.every), stream);
-    if (rc) {
-      adj_release(c);
-      return rc;
-    }
+  // The steps write a checkpointed state straight into its place in the store and read it
+  // from there; only the initial one is copied.
+  auto at = [&](int64_t t) -> double* {
+    return t % a.every == 0 && t / a.every < a.nckpt ? reinterpret_cast<double*>(a.mem + a.ckpt) + size_t(t / a.every) * a.state
+                                                     : nullptr;
+  };
+  if (a.nckpt > 0) rc = adj_save_state(c, at(0), s);
+  if (!rc) rc = do_steps(c, a.nsteps, stream, true, at);
+  if (rc) {
+    adj_release(c);
+    return rc;
   }
   HIP_TRY(hipStreamSynchronize(s));
   return VCLB_OK;
@@ -2388,7 +2412,7 @@ int vclb_adjoint_run(vclb_case* c, const double* seed, double normal_tau, double
   auto dptr = [&](size_t off) { return reinterpret_cast<double*>(M + off); };
   HIP_TRY(hipMemcpyAsync(dptr(st.seed), seed, size_t(nl) * vclb::kSeedFields * sizeof(double),
                          hipMemcpyHostToDevice, s));
-  if (vclb::launch_adj_zero(dptr(st.part), 2 * st.blocks, s)) return fail(VCLB_EHIP, "adjoint launch failed");
+  if (vclb::launch_adj_zero(dptr(st.part), 2 * st.slots, s)) return fail(VCLB_EHIP, "adjoint launch failed");
 
   vclb::DevCase<vclb::D2Q9, vclb::StoreF64> base = make_dev<vclb::D2Q9, vclb::StoreF64>(*c);
   base.t = 0;
@@ -2396,8 +2420,8 @@ int vclb_adjoint_run(vclb_case* c, const double* seed, double normal_tau, double
   base.part_r = nullptr;
   vclb::AdjArgs a{};
   a.lphi = dptr(st.lphi);
-  a.aux = dptr(st.aux);
   a.param_part = dptr(st.part);
+  a.part_slots = st.slots;
   a.seed = dptr(st.seed);
   a.beta4_per_sigma = 48.0 / c->p.W;
   a.kappa_per_sigma = 1.5 * c->p.W;
@@ -2413,24 +2437,27 @@ int vclb_adjoint_run(vclb_case* c, const double* seed, double normal_tau, double
     a.lg_out = dptr(st.lg[in ^ 1]);
     a.lf_out = dptr(st.lf[in ^ 1]);
     a.lJ_out = dptr(st.lJ[in ^ 1]);
+    a.aux_in = dptr(st.aux[in]);
+    a.aux_out = dptr(st.aux[in ^ 1]);
   };
   bind(1);   // the seed writes buffer 0
   int rc = vclb::launch_adj_seed(base, a, s);
-  auto slot = [&](int64_t k) { return dptr(st.seg) + size_t(k) * st.state; };
+  // states of the segment being recomputed; its first is the checkpoint itself
+  bool first = true;
   for (int64_t seg = st.nckpt - 1; seg >= 0 && !rc; --seg) {
+    auto slot = [&](int64_t k) {
+      return k == 0 ? dptr(st.ckpt) + size_t(seg) * st.state : dptr(st.seg) + size_t(k) * st.state;
+    };
     const int64_t t0 = seg * st.every, len = std::min<int64_t>(st.every, st.nsteps - t0);
-    HIP_TRY(hipMemcpyAsync(slot(0), dptr(st.ckpt) + size_t(seg) * st.state, st.state * sizeof(double),
-                           hipMemcpyDeviceToDevice, s));
     // recompute the segment's states with the forward step (no reductions)
     for (int64_t k = 0; k + 1 < len && !rc; ++k) {
-      HIP_TRY(hipMemcpyAsync(slot(k + 1) + 18 * ns, slot(k) + 18 * ns, 2 * ns * sizeof(double),
-                             hipMemcpyDeviceToDevice, s));
       auto f = base;
       f.pop[0][0] = slot(k);
       f.pop[1][0] = slot(k) + 9 * ns;
       f.pop[0][1] = slot(k + 1);
       f.pop[1][1] = slot(k + 1) + 9 * ns;
-      f.J = slot(k + 1) + 18 * ns;
+      f.J = slot(k) + 18 * ns;
+      f.Jw = slot(k + 1) + 18 * ns;
       rc = vclb::launch_step_fused<vclb::D2Q9, vclb::StoreF64, true>(f, c->tile, 0, s);
     }
     // backward through the segment
@@ -2442,16 +2469,17 @@ int vclb_adjoint_run(vclb_case* c, const double* seed, double normal_tau, double
       b.pop[1][1] = nullptr;
       b.J = slot(k) + 18 * ns;
       bind(cur);
-      rc = vclb::launch_phi_psi<vclb::D2Q9, vclb::StoreF64>(b, s);
-      if (!rc) rc = vclb::launch_adj_step(b, a, s);
+      rc = vclb::launch_adj_step(b, a, first, s);
+      first = false;
       cur ^= 1;
     }
   }
   if (rc) return fail(VCLB_EHIP, "adjoint launch failed");
   bind(cur);
   double* dst = (dphi0 && ptr_kind == VCLB_DEVICE) ? dphi0 : dptr(st.dphi);
-  rc = vclb::launch_adj_init(base, a, dptr(st.phi0), st.has_u0 ? dptr(st.u0) : nullptr, dst, s);
-  if (!rc) rc = vclb::launch_adj_params(a, int(st.blocks), dptr(st.out), s);
+  if (!first) rc = vclb::launch_adj_stencil(base, a, s);   // lphi of the first step; the seed's if there is none
+  if (!rc) rc = vclb::launch_adj_init(base, a, dptr(st.phi0), st.has_u0 ? dptr(st.u0) : nullptr, dst, s);
+  if (!rc) rc = vclb::launch_adj_params(a, dptr(st.out), s);
   if (rc) return fail(VCLB_EHIP, "adjoint launch failed");
   double host_out[2] = {0.0, 0.0};
   HIP_TRY(hipMemcpyAsync(host_out, dptr(st.out), sizeof(host_out), hipMemcpyDeviceToHost, s));

@@ -30,6 +30,8 @@ struct DevCase {
   double cen[kMaxLabels][3];    // label centres
   S* pop[2][2];                 // [g = 0, f = 1][buffer]; f is null in vortex mode
   R* J;                         // previous phi u, D planes of ns entries
+  R* Jw;                        // where the 2D steps of single cases write this step's (J itself
+                                // but in the adjoint's recorded and recomputed steps)
   float* phis[2];               // FP16S: phi of the node that wrote each buffer entry
   long t;                       // step index of the state this launch reads
   double* part_w;               // this launch's workgroup partials, [label * 12 + field][workgroup]

@@ -198,8 +198,8 @@ __device__ __forceinline__ void step2d_tile(const DevCase<D2Q9, St>& c, long t, 
           else St::store(c.pop[1][dst] + long(i) * ns, IX(nn), f[i]);
         }
       }
-      stg(c.J, IX(nn), J[0]);
-      stg(c.J + ns, IX(nn), J[1]);
+      stg(c.Jw, IX(nn), J[0]);
+      stg(c.Jw + ns, IX(nn), J[1]);
       if constexpr (St::shifted) stg(c.phis[dst], IX(nn), float(in.nphi[0] - res));
       if (reduce) {
         const double ph = double(in.nphi[0]);

@@ -145,8 +145,8 @@ __device__ __forceinline__ void tile2d_step(const DevCase<D2Q9, St>& c, long t, 
         else St::store(c.pop[1][dst] + long(i) * ns, nn, f[i]);
       }
     }
-    stg(c.J, nn, J[0]);
-    stg(c.J + ns, nn, J[1]);
+    stg(c.Jw, nn, J[0]);
+    stg(c.Jw + ns, nn, J[1]);
     if constexpr (St::shifted) stg(c.phis[dst], nn, float(in.nphi[0] - res));
   }
   // this tile's volume reductions, by one wave from the ring's phi: the helper, or the last
