@@ -339,10 +339,16 @@ int vclb_obs_seed(const vclb_obs* obs, int32_t nlabels, const double* weights, d
    selects ceil(sqrt(nsteps)). */
 int vclb_adjoint_bytes(const vclb_params* p, int64_t nsteps, int32_t every, size_t* bytes);
 
+/* Give the case device memory for the store of its next records (256-byte aligned, at
+   least vclb_adjoint_bytes of each, else they return VCLB_ENOMEM); borrowed until another
+   call gives other memory or NULL (the library allocates again) or the case is destroyed.
+   Drops a recorded pass.  No work of the case may be in flight. */
+int vclb_adjoint_set_store(vclb_case* c, void* mem, size_t bytes);
+
 /* Forward pass: vclb_case_init(phi0, u0), then nsteps fused steps, keeping a copy of the
    state (pulled g and f, previous phi u) every `every` steps (0: ceil(sqrt(nsteps))).
    The library allocates the store (vclb_adjoint_bytes; freed by the next record or by
-   vclb_case_destroy).  Afterwards the case holds the state at step nsteps.  Synchronises
+   vclb_case_destroy) unless the caller has given one.  Afterwards the case holds the state at step nsteps.  Synchronises
    the stream. */
 int vclb_adjoint_record(vclb_case* c, const double* phi0, const double* u0, int ptr_kind, int64_t nsteps,
                         int32_t every, void* stream);

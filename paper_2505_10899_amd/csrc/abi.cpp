@@ -230,6 +230,8 @@ struct vclb_case {
   int pend_nb = 0, pend_buf = 0;
   int64_t pend_step = 0;
   struct AdjStore* adj = nullptr;   // recorded forward pass of the adjoint (FP64 D2Q9 only)
+  void* adj_mem = nullptr;           // the caller's memory for its store, if any
+  size_t adj_mem_bytes = 0;
   void* lab_scratch = nullptr;       // scratch of the caller-label reductions (grown on demand)
   size_t lab_scratch_bytes = 0;
 };
@@ -1148,13 +1150,21 @@ int vclb_history(vclb_case* c, int64_t t_first, int32_t count, vclb_obs* out, vo
   if (int rc0 = flush_pending(c, s)) return rc0;
   const int nl = std::max(1, c->p.nlabels);
   const size_t row = size_t(nl) * vclb::kObsFields;
-  std::vector<double> all(size_t(vclb::kHistory) * row);
-  HIP_TRY(hipMemcpyAsync(all.data(), c->ws + c->lay.hist, all.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+  // the slots asked for, in step order (at most two copies: the ring wraps), not the whole
+  // ring: 100 steps of two labels are 21 KB of its 850
+  std::vector<double> all(size_t(count) * row);
+  for (int32_t k = 0; k < count;) {
+    const int64_t slot = (t_first + k) % vclb::kHistory;
+    const int32_t run = int32_t(std::min<int64_t>(count - k, vclb::kHistory - slot));
+    HIP_TRY(hipMemcpyAsync(all.data() + size_t(k) * row, c->ws + c->lay.hist + size_t(slot) * row * sizeof(double),
+                           size_t(run) * row * sizeof(double), hipMemcpyDeviceToHost, s));
+    k += run;
+  }
   HIP_TRY(hipStreamSynchronize(s));
   bool bad = false;
   for (int32_t k = 0; k < count; ++k) {
     const int64_t t = t_first + k;
-    unpack_obs(all.data() + size_t(t % vclb::kHistory) * row, nl, out + size_t(k) * nl);
+    unpack_obs(all.data() + size_t(k) * row, nl, out + size_t(k) * nl);
     for (int l = 0; l < nl; ++l) {
       if (out[size_t(k) * nl + l].step != t) return fail(VCLB_ESTATE, "history slot overwritten");
       bad = bad || out[size_t(k) * nl + l].nonfinite;
@@ -2205,6 +2215,7 @@ int vclb_batch_autotune(vclb_batch* b, const char* cache_path, int32_t steps, vo
 // recomputed, and the fields of the backward sweep.
 struct AdjStore {
   char* mem = nullptr;
+  bool own = true;   // allocated here, not the caller's
   int64_t nsteps = 0;
   int32_t every = 1;
   int64_t nckpt = 0;
@@ -2219,7 +2230,7 @@ namespace {
 
 void adj_release(vclb_case* c) {
   if (!c->adj) return;
-  if (c->adj->mem) (void)hipFree(c->adj->mem);
+  if (c->adj->mem && c->adj->own) (void)hipFree(c->adj->mem);
   delete c->adj;
   c->adj = nullptr;
 }
@@ -2342,6 +2353,16 @@ int vclb_adjoint_bytes(const vclb_params* p, int64_t nsteps, int32_t every, size
   return VCLB_OK;
 }
 
+int vclb_adjoint_set_store(vclb_case* c, void* mem, size_t bytes) {
+  if (!c) return fail(VCLB_EINVAL, "case is NULL");
+  if (mem && (reinterpret_cast<uintptr_t>(mem) % kAlign) != 0)
+    return fail(VCLB_EINVAL, "the store must be 256-byte aligned");
+  adj_release(c);
+  c->adj_mem = mem;
+  c->adj_mem_bytes = mem ? bytes : 0;
+  return VCLB_OK;
+}
+
 int vclb_adjoint_record(vclb_case* c, const double* phi0, const double* u0, int ptr_kind, int64_t nsteps,
                         int32_t every, void* stream) {
   if (!c || !phi0) return fail(VCLB_EINVAL, "case or phi0 is NULL");
@@ -2356,13 +2377,17 @@ int vclb_adjoint_record(vclb_case* c, const double* phi0, const double* u0, int 
   hipStream_t s = as_stream(stream);
   adj_release(c);
   AdjStore lay = adj_layout(c->p, nsteps, every);
-  void* m = nullptr;
-  hipError_t e = hipMalloc(&m, lay.total);
-  if (e != hipSuccess)
-    return fail(e == hipErrorOutOfMemory ? VCLB_ENOMEM : VCLB_EHIP, "hipMalloc of the adjoint store failed");
+  void* m = c->adj_mem;
+  lay.own = m == nullptr;
+  if (m && c->adj_mem_bytes < lay.total) return fail(VCLB_ENOMEM, "the adjoint store given is too small");
+  if (lay.own) {
+    const hipError_t e = hipMalloc(&m, lay.total);
+    if (e != hipSuccess)
+      return fail(e == hipErrorOutOfMemory ? VCLB_ENOMEM : VCLB_EHIP, "hipMalloc of the adjoint store failed");
+  }
   c->adj = new (std::nothrow) AdjStore(lay);
   if (!c->adj) {
-    (void)hipFree(m);
+    if (lay.own) (void)hipFree(m);
     return fail(VCLB_ENOMEM, "host allocation");
   }
   AdjStore& a = *c->adj;

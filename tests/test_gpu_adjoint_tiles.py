@@ -41,3 +41,45 @@ def test_gradients_match_complex_step(nx, ny, wall, nl):
         ref = float((OG.complex_step(p, phi0, u0, n, wrt, direction=d) * w).sum())
         print("  d/d%s: gpu %.12e complex step %.12e" % (wrt, val, ref), flush=True)
         assert abs(val - ref) <= TOL * max(abs(ref), 1e-3)
+
+
+@pytest.mark.parametrize("nsteps,every", [(0, 0), (1, 1), (13, 4)])
+def test_a_lent_store_gives_the_bits_of_the_library_s_own(nsteps, every):
+    """vclb_adjoint_set_store: exactly vclb_adjoint_bytes of memory; too little or misaligned
+    memory is refused; the binding's own record on another stream gives the same bits."""
+    import ctypes
+
+    import torch
+    from paper_2505_10899_amd import vclb as v
+    L = v.lib()
+    p = W.CaseParams(nx=33, ny=23, rho_light=0.3, W=3.0, label_centres=[(10.2, 11.1, 0.0)])
+    phi0 = torch.as_tensor(0.02 + 0.94 * W.drops_phi(p, [(10.2, 11.1, 0.0, 6.0)]), dtype=torch.float64, device="cuda").contiguous()
+    seed = np.ones((1, v.SEED_FIELDS))
+    n = ctypes.c_size_t()
+    v.check(L.vclb_adjoint_bytes(ctypes.byref(v.to_cparams(p)), nsteps, every, ctypes.byref(n)))
+    mem = torch.empty(n.value + 256, dtype=torch.uint8, device="cuda")
+    base = (mem.data_ptr() + 255) // 256 * 256
+
+    def record(c):
+        return L.vclb_adjoint_record(c.h, ctypes.c_void_p(phi0.data_ptr()), None, v.DEVICE, nsteps, every, v._stream_handle(None))
+
+    runs = []
+    c = v.Case(p)
+    for lend in (None, base, None):
+        v.check(L.vclb_adjoint_set_store(c.h, ctypes.c_void_p(lend), n.value))
+        with pytest.raises(v.VclbError):
+            c.adjoint_run(seed)                       # what was recorded is dropped
+        v.check(record(c))
+        dphi, ds, dm = c.adjoint_run(seed)
+        runs.append((dphi.cpu().numpy(), ds, dm))
+    assert L.vclb_adjoint_set_store(c.h, ctypes.c_void_p(base + 8), n.value) == v.VCLB_EINVAL
+    v.check(L.vclb_adjoint_set_store(c.h, ctypes.c_void_p(base), n.value - 1))
+    assert record(c) == v.VCLB_ENOMEM
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    c.adjoint_record(phi0, nsteps=nsteps, every=every, stream=s)
+    dphi, ds, dm = c.adjoint_run(seed, stream=s)
+    torch.cuda.synchronize()
+    runs.append((dphi.cpu().numpy(), ds, dm))
+    for r in runs[1:]:
+        assert np.array_equal(r[0], runs[0][0]) and r[1:] == runs[0][1:]

@@ -128,3 +128,17 @@ def test_batch_one_step(storage, visc):
     assert np.all(np.abs(h - np.array(sums)) <= rtol * (1.0 + np.abs(np.array(sums))))
     r = b.reduce()
     assert np.all(np.abs(r["sum_phi"][:, 0] - np.array(field())) <= rtol * (1.0 + np.abs(np.array(sums[1]))))
+
+
+def test_history_over_the_end_of_the_ring():
+    """The last HISTORY steps in one call (the ring wraps inside) equal single steps read
+    one by one before and after the wrap."""
+    from paper_2505_10899_amd import vclb
+    p = W.CaseParams(nx=8, ny=6, storage="fp32", label_centres=[(4.2, 3.1, 0.0)])
+    c = vclb.Case(p).init(W.drops_phi(p, [(4.2, 3.1, 0.0, 2.0)]))
+    c.step(vclb.HISTORY + 7)
+    h = c.history(7, vclb.HISTORY)
+    assert np.array_equal(h["step"][:, 0], np.arange(7, vclb.HISTORY + 7))
+    for t in (7, vclb.HISTORY - 1, vclb.HISTORY, vclb.HISTORY + 6):
+        one = c.history(t, 1)
+        assert all(np.array_equal(one[k][0], h[k][t - 7]) for k in one)
