@@ -152,7 +152,7 @@ int validate(const vclb_params* p) {
 }
 
 struct Layout {
-  size_t pop[2][2], J, phis[2], partials[2], hist, cur, tmp_phi, tmp_psi, mass, mass_part, total;
+  size_t pop[2][2], J[2], phis[2], partials[2], hist, cur, tmp_phi, tmp_psi, mass, mass_part, total;
   long partial_blocks;
 };
 
@@ -162,13 +162,24 @@ long partial_blocks_for(const vclb_params& p) {
   return long(size_t(p.nx) * p.ny * p.nz / 64) + long(p.ny) * p.nz + 64;
 }
 
+// Whether a case may take several steps in one launch (tile2d_multi): 2D, with few nodes.
+// It then has two buffers for J, by the parity of the step like the populations, and room
+// for the partial reductions of every step of a launch.
+constexpr long kMultiNodes = 1L << 16;
+bool multi_case(const vclb_params& p) {
+  return p.lattice == VCLB_D2Q9 && p.mass_fix <= 0 && long(p.nx) * p.ny <= kMultiNodes;
+}
+
 // the partial reductions of a 2D case's tiles fit the workspace (a grid of a few very long
 // rows has more tiles than that)
 bool tile2d_fits(const vclb_params& p, const vclb::Tile& t) {
+  if (vclb::tile2d_multi_ok(t.lx, t.ly))
+    return multi_case(p) && (t.lx == 3 || p.mode != VCLB_COUPLED || p.storage != VCLB_FP64);
   return vclb::fused_blocks(2, p.nx, p.ny, p.nz, t) <= partial_blocks_for(p);
 }
 
-Layout layout_for(const vclb_params& p) {
+// alone: not a case of a batch
+Layout layout_for(const vclb_params& p, bool alone = true) {
   Layout L{};
   const size_t n = size_t(p.nx) * p.ny * p.nz;
   const int Q = lattice_q(p.lattice), D = lattice_d(p.lattice);
@@ -187,9 +198,12 @@ Layout layout_for(const vclb_params& p) {
       const bool need = s == 0 || p.mode == VCLB_COUPLED;
       L.pop[s][b] = need ? take(size_t(Q) * ns * sb) : SIZE_MAX;
     }
-  L.J = take(size_t(D) * ns * rb);
+  L.J[0] = L.J[1] = take(size_t(D) * ns * rb);
+  if (alone && multi_case(p)) L.J[1] = take(size_t(D) * ns * rb);
   for (int b = 0; b < 2; ++b) L.phis[b] = p.storage != VCLB_FP64 ? take(n * 4) : SIZE_MAX;
   L.partial_blocks = partial_blocks_for(p);
+  if (L.J[1] != L.J[0])
+    L.partial_blocks = std::max(L.partial_blocks, 3 * vclb::fused_blocks(2, p.nx, p.ny, 1, vclb::Tile{256, 32, 4, 3, 3}));
   for (int b = 0; b < 2; ++b) L.partials[b] = take(size_t(L.partial_blocks) * nl * 12 * sizeof(double));
   L.hist = take(size_t(vclb::kHistory) * nl * vclb::kObsFields * sizeof(double));
   L.cur = take(size_t(nl) * vclb::kObsFields * sizeof(double));
@@ -228,6 +242,7 @@ struct vclb_case {
   // folds them in its first workgroup, anything that reads results flushes them first
   bool pending = false;
   int pend_nb = 0, pend_buf = 0;
+  int pend_mask = 1;               // bit k: step pend_step + k
   int64_t pend_step = 0;
   struct AdjStore* adj = nullptr;   // recorded forward pass of the adjoint (FP64 D2Q9 only)
   void* adj_mem = nullptr;           // the caller's memory for its store, if any
@@ -274,7 +289,9 @@ vclb::DevCase<L, St> make_dev(const vclb_case& c) {
   for (int s = 0; s < 2; ++s)
     for (int b = 0; b < 2; ++b)
       d.pop[s][b] = c.lay.pop[s][b] == SIZE_MAX ? nullptr : reinterpret_cast<S*>(c.ws + c.lay.pop[s][b]);
-  d.J = d.Jw = reinterpret_cast<R*>(c.ws + c.lay.J);
+  d.J = reinterpret_cast<R*>(c.ws + c.lay.J[c.t_host & 1]);
+  d.Jw = reinterpret_cast<R*>(c.ws + c.lay.J[(c.t_host + 1) & 1]);
+  d.steps = 1;
   for (int b = 0; b < 2; ++b)
     d.phis[b] = c.lay.phis[b] == SIZE_MAX ? nullptr : reinterpret_cast<float*>(c.ws + c.lay.phis[b]);
   d.t = long(c.t_host);
@@ -283,7 +300,9 @@ vclb::DevCase<L, St> make_dev(const vclb_case& c) {
   d.pend_nb = 0;
   d.pend_dest = nullptr;
   d.pend_step = 0;
+  d.pend_mask = 1;
   if (c.pending) {
+    d.pend_mask = c.pend_mask;
     d.part_r = reinterpret_cast<const double*>(c.ws + c.lay.partials[c.pend_buf]);
     d.pend_nb = c.pend_nb;
     d.pend_dest = reinterpret_cast<double*>(c.ws + c.lay.hist) +
@@ -370,7 +389,16 @@ int flush_pending(vclb_case* c, hipStream_t s) {
   if (!c->pending) return VCLB_OK;
   int rc = dispatch(*c, [&](auto dc, auto) {
     using DC = decltype(dc);
-    return vclb::launch_finalize<typename DevTraits<DC>::L, typename DevTraits<DC>::St>(dc, s);
+    const double* part = dc.part_r;
+    int rc1 = 0;
+    for (int k = 0; c->pend_mask >> k && !rc1; ++k) {   // a step each
+      if (!(c->pend_mask >> k & 1)) continue;
+      dc.part_r = part + size_t(k) * dc.nl * 12 * dc.pend_nb;
+      dc.pend_step = long(c->pend_step + k);
+      dc.pend_dest = dc.hist + (dc.pend_step % vclb::kHistory) * dc.nl * vclb::kObsFields;
+      rc1 = vclb::launch_finalize<typename DevTraits<DC>::L, typename DevTraits<DC>::St>(dc, s);
+    }
+    return rc1;
   });
   c->pending = false;
   return rc ? fail(VCLB_EHIP, "finalize launch failed") : VCLB_OK;
@@ -379,8 +407,13 @@ int flush_pending(vclb_case* c, hipStream_t s) {
 // Whether a 2D case steps with one lane per node (tile2d.hip) or as a row march, and in
 // which tile.  Measured on square and oblong grids of 66 x 24 to 4096 x 4096, coupled and
 // vortex, each storage (us a step, march / tile):
-//  - 16 x 8 nodes and a helper wave up to 2^19 nodes, where the chain of one launch counts
-//    (512 x 256 FP32 42 / 7.1; 64 x 4 tiles 8.0);
+//  - up to one workgroup per CU, where the chain of one launch is all there is, three steps in
+//    a launch: 8 x 8 nodes (128 x 128 FP64 31 / 3.6, FP32 2.7, one step a launch 5.3 and 4.7), or
+//    16 x 16 (256 x 256 FP32 4.4 against 5.4, vortex FP64 4.5 against 6.4).  With a second
+//    workgroup on the CUs the halo's repeated work costs more than the launches (144 x 144 FP64
+//    coupled 5.9 against 5.5, 300 x 300 FP64 vortex 7.7 and 7.8);
+//  - 16 x 8 nodes and a helper wave up to 2^19 nodes, where the chain of one launch still
+//    counts (512 x 256 FP32 42 / 6.9; 64 x 4 tiles 8.0);
 //  - 64 x 4 while both population sets fit the 256 MB last-level cache (777 x 1333 FP32
 //    62 / 30), 128 x 4 beyond, whose halo is a smaller share (2048 x 2048 FP64 275 / 248,
 //    2051 x 2043 FP32 227 / 161);
@@ -389,7 +422,7 @@ int flush_pending(vclb_case* c, hipStream_t s) {
 //    352 / 361; 2944 x 2944 FP32 289 / 302), except FP32 rows that do not start on cache
 //    lines (4091 x 4096 FP32 650 / 637);
 //  - beyond 2^26 nodes the tiles' 32-bit byte offsets end (three planes of 8 bytes).
-void tile2d_choose(const vclb_params& p, vclb::Tile& t) {
+void tile2d_choose(const vclb_params& p, vclb::Tile& t, bool multi) {
   t.lx = t.ly = 0;
   const long n = long(p.nx) * p.ny;
   const size_t sb = storage_bytes(p.storage);
@@ -399,7 +432,10 @@ void tile2d_choose(const vclb_params& p, vclb::Tile& t) {
   if (p.storage != VCLB_FP64 && n >= (1L << 23) && !(p.storage == VCLB_FP32 && coupled && !lines)) return;
   const size_t sets = size_t(n) * 9 * sb * (coupled ? 4 : 2);
   vclb::Tile u = t;
-  if (n <= (1L << 19)) u.lx = 4, u.ly = 3;
+  auto one_per_cu = [&](int side) { return long((p.nx + side - 1) / side) * ((p.ny + side - 1) / side) <= 256; };
+  if (multi && multi_case(p) && one_per_cu(8)) u.lx = u.ly = 3;
+  else if (multi && tile2d_fits(p, vclb::Tile{t.bx, t.ty, t.by3, 4, 4}) && one_per_cu(16)) u.lx = u.ly = 4;
+  else if (n <= (1L << 19)) u.lx = 4, u.ly = 3;
   else if (sets <= (size_t(256) << 20)) u.lx = 6, u.ly = 2;
   else u.lx = 7, u.ly = 2;
   if (tile2d_fits(p, u)) t = u;
@@ -418,7 +454,7 @@ bool flat3d_chosen(const vclb_params& p) {
   return !(p.storage != VCLB_FP16S && lines && n >= (1L << 21));
 }
 
-vclb::Tile default_tile(const vclb_params& p, int ncu, bool wide_ok = true) {
+vclb::Tile default_tile(const vclb_params& p, int ncu, bool wide_ok = true, bool multi = true) {
   vclb::Tile t;
   if (p.lattice == VCLB_D2Q9) {
     // one lane per x column, rounded up to whole waves, at most 256 lanes, or 512 with
@@ -439,7 +475,7 @@ vclb::Tile default_tile(const vclb_params& p, int ncu, bool wide_ok = true) {
     const long ty = (long(p.ny) + segs - 1) / segs;
     t.ty = int(std::max(8L, std::min(64L, ty)));
     t.by3 = 1;
-    tile2d_choose(p, t);
+    tile2d_choose(p, t, multi);
   } else {
     // 32 x 8 columns per workgroup (a halo ring of a third of the tile, one wave per two
     // rows of 32): the fastest section measured on a 96 x 96 x 384 case.  Each workgroup
@@ -572,12 +608,13 @@ int vclb_case_workspace_bytes(const vclb_params* p, size_t* bytes) {
   return VCLB_OK;
 }
 
-int vclb_case_create(const vclb_params* p, void* workspace, size_t workspace_bytes, vclb_case** out) {
+// alone: not a case of a batch
+static int case_create(const vclb_params* p, void* workspace, size_t workspace_bytes, bool alone, vclb_case** out) {
   int rc = validate(p);
   if (rc) return rc;
   if (!out) return fail(VCLB_EINVAL, "out is NULL");
   *out = nullptr;
-  const Layout lay = layout_for(*p);
+  const Layout lay = layout_for(*p, alone);
   if (workspace && workspace_bytes < lay.total) return fail(VCLB_ENOMEM, "workspace too small");
   if (workspace && (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0)
     return fail(VCLB_EINVAL, "workspace must be 256-byte aligned");
@@ -590,8 +627,8 @@ int vclb_case_create(const vclb_params* p, void* workspace, size_t workspace_byt
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       ncu < 1)
     ncu = 256;
-  c->tile = default_tile(c->p, ncu);
-  if (check_tile(c->p, c->tile) != VCLB_OK) c->tile = default_tile(c->p, ncu, false);   // no wide 3D section here
+  c->tile = default_tile(c->p, ncu, true, alone);
+  if (check_tile(c->p, c->tile) != VCLB_OK) c->tile = default_tile(c->p, ncu, false, alone);   // no wide 3D section here
   c->recorded.assign(vclb::kHistory, -1);
   if (workspace) {
     c->ws = static_cast<char*>(workspace);
@@ -607,6 +644,10 @@ int vclb_case_create(const vclb_params* p, void* workspace, size_t workspace_byt
   }
   *out = c;
   return VCLB_OK;
+}
+
+int vclb_case_create(const vclb_params* p, void* workspace, size_t workspace_bytes, vclb_case** out) {
+  return case_create(p, workspace, workspace_bytes, true, out);
 }
 
 void vclb_case_destroy(vclb_case* c) {
@@ -689,6 +730,7 @@ int vclb_case_init(vclb_case* c, const double* phi0, const double* u0, int ptr_k
     using DC = decltype(dc);
     using L = typename DevTraits<DC>::L;
     using St = typename DevTraits<DC>::St;
+    dc.J = reinterpret_cast<decltype(dc.J)>(c->ws + c->lay.J[0]);   // of step 0
     return vclb::launch_init<L, St, decltype(coupled)::value>(dc, dphi, du, s);
   });
   if (staging) {
@@ -734,6 +776,7 @@ int vclb_case_set_state(vclb_case* c, const double* g, const double* f, const do
   }
   int rc = dispatch(*c, [&](auto dc, auto cp) {
     using DC = decltype(dc);
+    dc.J = reinterpret_cast<decltype(dc.J)>(c->ws + c->lay.J[t & 1]);
     return vclb::launch_set_state<typename DevTraits<DC>::L, typename DevTraits<DC>::St, decltype(cp)::value>(
         dc, dg, df, dJ, long(t), s);
   });
@@ -802,14 +845,22 @@ static int do_steps(vclb_case* c, int64_t nsteps, void* stream, bool fused,
     int rc = flush_pending(c, s);
     if (rc) return rc;
   }
-  for (int64_t k = 0; k < nsteps; ++k) {
+  // three steps in one launch: an odd number, so that the state keeps to the buffers of its parity
+  const bool multi = fused && c->p.lattice == VCLB_D2Q9 && vclb::tile2d_multi_ok(c->tile.lx, c->tile.ly);
+  for (int64_t k = 0, n = 1; k < nsteps; k += n) {
     const int64_t t = c->t_host;
-    const int reduce = (c->reduce_every > 0 && t % c->reduce_every == 0) ? 1 : 0;
+    n = multi && !place && nsteps - k >= 3 ? 3 : 1;
+    int reduce = 0;   // bit j: record the reductions of step t + j
+    for (int64_t j = 0; j < n; ++j)
+      if (c->reduce_every > 0 && (t + j) % c->reduce_every == 0) reduce |= 1 << j;
+    if (c->pending && c->pend_mask > 1 && !multi)
+      if (int rc = flush_pending(c, s)) return rc;
     int rc = dispatch(*c, [&](auto dc, auto coupled) {
       using DC = decltype(dc);
       using L = typename DevTraits<DC>::L;
       using St = typename DevTraits<DC>::St;
       constexpr bool C = decltype(coupled)::value;
+      dc.steps = int(n);
       if constexpr (std::is_same<DC, vclb::DevCase<vclb::D2Q9, vclb::StoreF64>>::value) {
         if (place) {
           const int par = int(t & 1);
@@ -834,8 +885,10 @@ static int do_steps(vclb_case* c, int64_t nsteps, void* stream, bool fused,
     c->pend_nb = int(blocks);
     c->pend_buf = int(t & 1);
     c->pend_step = t;
-    if (reduce) c->recorded[size_t(t % vclb::kHistory)] = t;
-    c->t_host = t + 1;
+    c->pend_mask = reduce;
+    for (int64_t j = 0; j < n; ++j)
+      if (reduce >> j & 1) c->recorded[size_t((t + j) % vclb::kHistory)] = t + j;
+    c->t_host = t + n;
   }
   return VCLB_OK;
 }
@@ -846,6 +899,7 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
   if (!c || steps < 1) return fail(VCLB_EINVAL, "bad autotune arguments");
   if (!c->inited) return fail(VCLB_ESTATE, "autotune needs an initialised case (its state is restored)");
   const vclb_params& p = c->p;
+  const bool alone = c->lay.J[0] != c->lay.J[1];   // may take several steps in a launch
   const std::string desc = "case:" + std::to_string(p.lattice) + ":" + std::to_string(p.storage) + ":" +
                            std::to_string(p.mode) + ":" + std::to_string(p.nx) + "x" + std::to_string(p.ny) + "x" +
                            std::to_string(p.nz) + (wall_y(p) ? "w" : "p") + std::to_string(std::max(1, p.nlabels));
@@ -878,7 +932,7 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
         t.lx = lx;
         t.ly = ly;
         if (!rc && p.lattice == VCLB_D2Q9 && vclb::tile2d_shape_ok(lx, ly) && long(p.nx) * p.ny <= (1L << 26) &&
-            tile2d_fits(p, t))
+            tile2d_fits(p, t) && (!vclb::tile2d_multi_ok(lx, ly) || alone))
           c->tile = t;
         if (!rc && flat && p.lattice == VCLB_D3Q19 && default_tile(p, 256).flat) c->tile.flat = true;
         return rc;
@@ -889,11 +943,12 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
   // their z extent cut into as many segments as fill 1..4 workgroups per CU once
   std::vector<vclb::Tile> cands;
   if (p.lattice == VCLB_D2Q9) {
-    // where tiles of one lane per node are the default, their three shapes too; elsewhere
+    // where tiles of one lane per node are the default, their shapes too; elsewhere
     // every candidate is a march, whose results do not depend on the shape
     const vclb::Tile def = default_tile(p, 256);
     if (def.lx > 0)
-      for (const auto& sh : {std::pair<int, int>{4, 3}, {6, 2}, {7, 2}}) {
+      for (const auto& sh : {std::pair<int, int>{3, 3}, {4, 4}, {4, 3}, {6, 2}, {7, 2}}) {
+        if (vclb::tile2d_multi_ok(sh.first, sh.second) && !alone) continue;
         vclb::Tile t = def;
         t.lx = sh.first;
         t.ly = sh.second;
@@ -1196,7 +1251,7 @@ std::vector<Span> state_spans(const vclb_case* c, int par) {
   std::vector<Span> v;
   v.push_back({c->lay.pop[0][par], size_t(Q) * ns * storage_bytes(c->p.storage)});
   if (c->p.mode == VCLB_COUPLED) v.push_back({c->lay.pop[1][par], size_t(Q) * ns * storage_bytes(c->p.storage)});
-  v.push_back({c->lay.J, size_t(D) * ns * arith_bytes(c->p.storage)});
+  v.push_back({c->lay.J[par], size_t(D) * ns * arith_bytes(c->p.storage)});
   if (c->p.storage != VCLB_FP64) v.push_back({c->lay.phis[par], n * 4});
   v.push_back({c->lay.mass, sizeof(double)});   // V_ref of the global volume correction
   return v;
@@ -1653,7 +1708,7 @@ int vclb_batch_create(const vclb_params* cases, int32_t ncases, vclb_batch** out
   size_t cap = 0;
   for (int k = 0; k < ncases; ++k) {
     off[size_t(k)] = total;
-    total += align_up(layout_for(cases[k]).total);
+    total += align_up(layout_for(cases[k], false).total);
     cap += size_t(cases[k].ny) * size_t((cases[k].nx + 63) / 64);   // at most one item per row and strip
     b->nodes += int64_t(cases[k].nx) * cases[k].ny;
   }
@@ -1711,7 +1766,7 @@ int vclb_batch_create(const vclb_params* cases, int32_t ncases, vclb_batch** out
   for (int i = 0; i < 2; ++i) b->part[i] = reinterpret_cast<double*>(b->ws + o_part[i]);
   for (int k = 0; k < ncases; ++k) {
     vclb_case* c = nullptr;
-    int rc = vclb_case_create(&cases[k], b->ws + off[size_t(k)], layout_for(cases[k]).total, &c);
+    int rc = case_create(&cases[k], b->ws + off[size_t(k)], layout_for(cases[k], false).total, false, &c);
     if (rc) {
       vclb_batch_destroy(b);
       return rc;
@@ -2286,7 +2341,7 @@ int adj_save_state(vclb_case* c, double* dst, hipStream_t s) {
   const int par = int(c->t_host & 1);
   HIP_TRY(hipMemcpyAsync(dst, c->ws + c->lay.pop[0][par], 9 * ns * sizeof(double), hipMemcpyDeviceToDevice, s));
   HIP_TRY(hipMemcpyAsync(dst + 9 * ns, c->ws + c->lay.pop[1][par], 9 * ns * sizeof(double), hipMemcpyDeviceToDevice, s));
-  HIP_TRY(hipMemcpyAsync(dst + 18 * ns, c->ws + c->lay.J, 2 * ns * sizeof(double), hipMemcpyDeviceToDevice, s));
+  HIP_TRY(hipMemcpyAsync(dst + 18 * ns, c->ws + c->lay.J[par], 2 * ns * sizeof(double), hipMemcpyDeviceToDevice, s));
   return VCLB_OK;
 }
 

@@ -30,8 +30,8 @@ struct DevCase {
   double cen[kMaxLabels][3];    // label centres
   S* pop[2][2];                 // [g = 0, f = 1][buffer]; f is null in vortex mode
   R* J;                         // previous phi u, D planes of ns entries
-  R* Jw;                        // where the 2D steps of single cases write this step's (J itself
-                                // but in the adjoint's recorded and recomputed steps)
+  R* Jw;                        // where a step writes the next ones: J itself, or another buffer for
+                                // small 2D cases and the adjoint's recorded and recomputed steps
   float* phis[2];               // FP16S: phi of the node that wrote each buffer entry
   long t;                       // step index of the state this launch reads
   double* part_w;               // this launch's workgroup partials, [label * 12 + field][workgroup]
@@ -39,6 +39,9 @@ struct DevCase {
   int pend_nb;                  // workgroups of that launch, 0 if none pending
   double* pend_dest;            // where its sums go: [label][kObsFields]
   long pend_step;               // the step it belongs to
+  int pend_mask;                // bit k: the partials of step pend_step + k are there, nl * 12 *
+                                // pend_nb entries apart (1 but after several steps in one launch)
+  int steps;                    // steps of this launch (tile2d_multi), else 1
   double* hist;                 // [kHistory][label][kObsFields]
   double* cur;                  // [label][kObsFields] reductions of the current state
   R* tmp_phi;                   // scratch N: phi (plain path and observe)
@@ -347,7 +350,7 @@ __device__ __forceinline__ void store_node(const DevCase<L, St>& c, int par, lon
     for (int i = 0; i < L::Q; ++i) St::store(c.pop[1][dst], long(i) * c.ns + n, f[i]);
   }
 #pragma unroll
-  for (int d = 0; d < L::D; ++d) stg(c.J, d * c.ns + n, J[d]);
+  for (int d = 0; d < L::D; ++d) stg(c.Jw, d * c.ns + n, J[d]);
   if constexpr (St::shifted) stg(c.phis[dst], n, float(phi - res));
 }
 

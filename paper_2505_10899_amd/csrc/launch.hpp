@@ -27,9 +27,14 @@ int launch_step_plain(const DevCase<L, St>& c, int reduce, hipStream_t s);
 template <class L, class St, bool COUPLED>
 int launch_step_fused(const DevCase<L, St>& c, const Tile& tile, int reduce, hipStream_t s);
 // D2Q9 tiles of 2^lx x 2^ly nodes, one lane per node (tile2d.hip): 16 x 8 with a helper
-// wave, 64 x 4 and 128 x 4
+// wave, 64 x 4 and 128 x 4, and the two shapes of tile2d_multi
 inline bool tile2d_helper(int lx, int ly) { return lx == 4; }
-inline bool tile2d_shape_ok(int lx, int ly) { return (lx == 4 && ly == 3) || ((lx == 6 || lx == 7) && ly == 2); }
+// 8 x 8 and 16 x 16 (but for coupled FP64, whose state between two steps exceeds 64 KiB): up
+// to three steps in one launch (tile2d_multi)
+inline bool tile2d_multi_ok(int lx, int ly) { return (lx == 3 && ly == 3) || (lx == 4 && ly == 4); }
+inline bool tile2d_shape_ok(int lx, int ly) {
+  return tile2d_multi_ok(lx, ly) || (lx == 4 && ly == 3) || ((lx == 6 || lx == 7) && ly == 2);
+}
 template <class St, bool COUPLED>
 int launch_tile2d(const DevCase<D2Q9, St>& c, int lx, int ly, int reduce, hipStream_t s);
 template <class L, class St, bool COUPLED>

@@ -82,6 +82,8 @@ struct StoreF64 {
   static constexpr bool shifted = false;
   static constexpr bool fold = false;
   __device__ static R rounding(R) { return R(0); }
+  __device__ static S enc(R v) { return v; }
+  __device__ static R dec(S v) { return v; }
   template <class I>
   __device__ static R load(const S* p, I i) { return ldg(p, i); }
   template <class I>
@@ -100,6 +102,8 @@ struct StoreF32 {
   static constexpr bool shifted = true;
   static constexpr bool fold = false;
   __device__ static R rounding(R) { return R(0); }
+  __device__ static S enc(R v) { return v; }
+  __device__ static R dec(S v) { return v; }
   template <class I>
   __device__ static R load(const S* p, I i) { return ldg(p, i); }
   template <class I>
@@ -126,6 +130,8 @@ struct StoreF16S {
   // total of the decoded populations stays the total of phi.
   static constexpr bool fold = true;
   __device__ static R rounding(R v) { return __half2float(__float2half_rn(v)) - v; }
+  __device__ static S enc(R v) { return __float2half_rn(v); }
+  __device__ static R dec(S v) { return __half2float(v); }
   template <class I>
   __device__ static R load(const S* p, I i) {
     return __half2float(__ushort_as_half(ldg(reinterpret_cast<const unsigned short*>(p), i)));

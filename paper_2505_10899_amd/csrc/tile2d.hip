@@ -1,5 +1,5 @@
-// One D2Q9 step with one lane per node: the step of single cases whose grid does not keep
-// the row march of step2d.hpp busy.
+// D2Q9 steps with one lane per node: the step of single cases whose grid does not keep the
+// row march of step2d.hpp busy, and of batches of few nodes.
 //
 // A march hides its memory round trips behind the rows that follow; a grid of a few
 // hundred thousand nodes leaves each workgroup only a handful of rows, and the step then
@@ -7,13 +7,16 @@
 // nodes, every lane requests all populations of its node and its share of the halo ring's
 // g at once, phi and psi go to LDS, and after one barrier every lane updates its node: one
 // round trip per step, and with nothing carried from row to row 54 registers in FP32 and
-// 92 in FP64, so that 8 and 5 waves per SIMD hide it.  Measured per step, march against
-// tiles, with the reductions:
-//   66 x 24 FP32 (walls)   29 -> 4.9 us      128 x 128 FP64   31 -> 5.9 us
-//   512 x 256 FP64         47 -> 9.7 us      777 x 1333 FP32  62 -> 30 us (36.7 GLUPS)
-//   1501 x 1003 FP16S      40 -> 29 us       2048 x 2048 FP64 275 -> 248 us
-// Small tiles are bound by the chain of one launch: dispatch, pull, stencil, update, store
-// (about 5 us); large ones by memory.
+// 92 in FP64, so that 8 and 5 waves per SIMD hide it.  On the smallest grids, where the
+// chain of a launch (dispatch, pull, stencil, update, store: 5 us) is nearly all of a step,
+// a launch takes three (tile2d_multi).  Measured per step, march against tiles, with the
+// reductions:
+//   66 x 24 FP32 (walls)   29 -> 4.7 us, in threes 2.7
+//   128 x 128 FP64         31 -> 5.2, in threes 3.6
+//   256 x 256 FP64 vortex  32 -> 6.4, in threes 4.5
+//   512 x 256 FP64         47 -> 9.5 us      777 x 1333 FP32  62 -> 29 us (36 GLUPS)
+//   1501 x 1003 FP16S      40 -> 28 us       2048 x 2048 FP64 275 -> 246 us
+// Large ones are bound by memory.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -46,23 +49,56 @@ __global__ void __launch_bounds__(tile2d_lanes(LX, LY, HELP))
   tile2d_step<St, COUPLED, UNIT, VISC, LX, LY, HELP, NT>(c, c.t, tile, ntx, reduce ? c.part_w + tile : nullptr, ntiles);
 }
 
+// Up to three steps in one launch (tile2d_multi).  As above, the first workgroups sum the
+// partials of the launch before, of one step or of up to three.
+template <class St, bool COUPLED, bool UNIT, bool VISC, int LX, int LY>
+__global__ void __launch_bounds__(tile2d_multi_lanes(LX, LY))
+    k_tile2d_multi(DevCase<D2Q9, St> c, int ntx, int ntiles, int reduce) {
+  constexpr int kFields = 8;
+  constexpr int field[kFields] = {0, 1, 2, 3, 5, 6, 8, 11};
+  const int per_set = c.nl * kFields;
+  const int extra = c.pend_nb > 0 ? per_set * (c.pend_mask > 1 ? kMultiSteps : 1) : 0;
+  if (int(blockIdx.x) < extra) {
+    const int set = blockIdx.x / per_set, b = blockIdx.x - set * per_set;
+    if (!(c.pend_mask >> set & 1)) return;
+    const int k = b / kFields, j = b % kFields;
+    const long step = c.pend_step + set;
+    double* dest = c.hist + (step % kHistory) * c.nl * kObsFields;
+    fold_field(c.part_r + long(set) * c.nl * 12 * c.pend_nb, c.pend_nb, dest, step, k, field[j]);
+    if (j == 0 && threadIdx.x < 4) {
+      constexpr int zero[4] = {4, 7, 9, 10};
+      dest[k * kObsFields + zero[threadIdx.x]] = 0.0;
+    }
+    return;
+  }
+  const int tile = xcd_tile(int(blockIdx.x) - extra, ntiles);
+  tile2d_multi<St, COUPLED, UNIT, VISC, LX, LY>(c, c.t, c.steps, tile, ntx, reduce, c.part_w + tile, ntiles,
+                                                long(c.nl) * 12 * ntiles);
+}
+
 template <class St, bool COUPLED>
 int launch_tile2d(const DevCase<D2Q9, St>& c, int lx, int ly, int reduce, hipStream_t s) {
-  if (!tile2d_shape_ok(lx, ly)) return -1;
+  using R = typename St::R;
+  if (!tile2d_shape_ok(lx, ly) || (lx == 4 && ly == 4 && COUPLED && sizeof(R) == 8)) return -1;
   const int ntx = (c.nx + (1 << lx) - 1) >> lx, nty = (c.ny + (1 << ly) - 1) >> ly;
   const int ntiles = ntx * nty, lanes = 1 << (lx + ly);
   const bool help = tile2d_helper(lx, ly);
   // the non-temporal hint where it pays: rows of whole cache lines (every store of a wave
   // fills its lines; else the hint evicts lines that the next tile completes, 2951 x 2937
   // FP32 348 -> 420 us) of grids whose two population sets exceed the 256 MB last-level
-  // cache (2048 x 2048 FP32 145 -> 131, FP64 268 -> 248; within it 1024 x 1024 FP32 29.5 -> 43)
+  // cache (2048 x 2048 FP32 145 -> 131, FP64 268 -> 246; within it 1024 x 1024 FP32 29.5 -> 43)
   const size_t set = size_t(c.ns) * 9 * sizeof(typename St::S) * (COUPLED ? 4 : 2);
   const bool nt = lx == 7 && size_t(c.nx) * sizeof(typename St::S) % 128 == 0 && set > (size_t(256) << 20);
-  const dim3 grid(unsigned(ntiles + (c.pend_nb > 0 ? c.nl * 8 : 0))), block(unsigned(lanes + (help ? 64 : 0)));
+  const int sets = c.pend_mask > 1 ? kMultiSteps : 1;
+  const dim3 grid(unsigned(ntiles + (c.pend_nb > 0 ? c.nl * 8 * sets : 0)));
+  const dim3 block(unsigned(tile2d_multi_ok(lx, ly) ? tile2d_multi_lanes(lx, ly) : lanes + (help ? 64 : 0)));
   auto go = [&](auto unit, auto visc) {
     constexpr bool U = decltype(unit)::value, V = decltype(visc)::value;
     auto run = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, s, c, ntx, ntiles, reduce); };
-    if (help) run(k_tile2d<St, COUPLED, U, V, 4, 3, true, false>);
+    constexpr bool kWide = !COUPLED || sizeof(R) == 4;   // LDS of 16 x 16 tiles
+    if (lx == 3) run(k_tile2d_multi<St, COUPLED, U, V, 3, 3>);
+    else if (lx == 4 && ly == 4) run(k_tile2d_multi<St, COUPLED, U, V, kWide ? 4 : 3, kWide ? 4 : 3>);
+    else if (help) run(k_tile2d<St, COUPLED, U, V, 4, 3, true, false>);
     else if (lx == 6) run(k_tile2d<St, COUPLED, U, V, 6, 2, false, false>);
     else if (nt) run(k_tile2d<St, COUPLED, U, V, 7, 2, false, true>);
     else run(k_tile2d<St, COUPLED, U, V, 7, 2, false, false>);
