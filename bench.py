@@ -8,8 +8,7 @@ log-uniform in [64, 512], PCG64 seed 10899), advanced together.  One step is one
 of the whole hot path over every case: pull streaming with bounce-back/moving walls,
 phi and psi with their LDS halo, the gradient/Laplacian/normal stencils, chemical
 potential, velocity and pressure, g and f collisions with the level-set source, and
-the per-case FP64 volume reductions, as one work-list kernel per step; a call's steps
-are replayed from one hipGraph.  The tile is chosen by the library's autotuner, and the
+the per-case FP64 volume reductions, as one work-list kernel per step.  The tile is chosen by the library's autotuner, and the
 runs of work items are then re-cut to the measured speed of each workgroup slot.  The
 batch is timed for each storage precision; `value` is the FP32-storage rate (FP32
 arithmetic), FP16-shifted and FP64 are under `variants`.
@@ -67,7 +66,7 @@ KERNEL = {"fp64": "k_batch_step2d<StoreF64>", "fp32": "k_batch_step2d<StoreF32>"
 BATCH_DESC = ("512 independent D2Q9 coupled drop cases, sides log-uniform in [64, 512] (independent "
               "nx, ny), radius 0.1-0.3 of the shorter side, density ratio log-uniform in [1, 100], static "
               "periodic or shear between walls moving +-0.02 (1/2 each), W = 4, M = 0.1, sigma = 0.01, "
-              "nu = 0.1; PCG64 seed 10899; one work-list kernel per step, hipGraph replay")
+              "nu = 0.1; PCG64 seed 10899; one work-list kernel per step")
 
 
 def log(msg):

@@ -209,8 +209,10 @@ int vclb_case_create(const vclb_params* p, void* workspace, size_t workspace_byt
 void vclb_case_destroy(vclb_case* c);
 
 /* Tile of the fused step kernel.  By default a D2Q9 case that the march below would leave
-   waiting for its row round trips steps in tiles of one lane per node instead; get_tile
-   returns the march's shape all the same, and set_tile chooses the march.  D2Q9: bx lanes (x columns; a multiple of 64 in
+   waiting for its row round trips steps in tiles of one lane per node instead (the smallest
+   three steps per launch), and a D3Q19 case whose rows or size do not suit the march, or
+   with FP16S storage, in two passes in stored order; get_tile returns the march's shape all
+   the same, and set_tile chooses the march.  D2Q9: bx lanes (x columns; a multiple of 64 in
    64..256, or 512 or 1024 with FP32 or FP16S storage) marching ty >= 1 rows of y (by3
    ignored).  D3Q19: a bx x by3 section of (x, y)
    columns (bx * by3 a multiple of 64, at most 256, or at most 768 with FP32 or FP16S
@@ -226,7 +228,8 @@ int vclb_case_get_tile(const vclb_case* c, int32_t* bx, int32_t* ty, int32_t* by
    lattice, storage, mode, shape, boundary and label count; a measured choice is appended
    to cache_path (NULL: no file).  D2Q9 candidates: bx in {64, 128, 256} (and 512, 1024
    with 4-byte storage) x ty in {8, ..., 128}, and, for a case that steps in tiles of one
-   lane per node by default, three such tiles; D3Q19: six column sections with their
+   lane per node by default, the tile shapes of its size; D3Q19: the two passes, where they
+   are the default, and six column sections with their
    planes cut to fill 1..4 workgroups per CU, and (4-byte storage) three 768-lane
    sections at one per CU.  Synchronises the stream; VCLB_ESTATE before init. */
 int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void* stream);
@@ -247,8 +250,9 @@ int vclb_case_set_state(vclb_case* c, const double* g, const double* f, const do
 /* The current state in the layout of vclb_case_set_state, decoded to FP64. */
 int vclb_case_get_state(vclb_case* c, double* g, double* f, double* J, int ptr_kind, void* stream);
 
-/* Advance nsteps >= 0 time steps with the fused single-kernel step (pull streaming,
-   LDS-staged phi/psi halo tiles, fused reductions).  Asynchronous. */
+/* Advance nsteps >= 0 time steps with the fused step (pull streaming, LDS-staged phi/psi
+   halo tiles, fused reductions), or the D3Q19 two passes.  The results do not depend on how
+   steps are split between calls.  Asynchronous. */
 int vclb_step(vclb_case* c, int64_t nsteps, void* stream);
 
 /* Same update with the plain two-kernel path (phi/psi pass, then stencil + collision

@@ -239,7 +239,7 @@ struct vclb_case {
   bool inited = false;
   std::vector<int64_t> recorded;   // step recorded in each history slot (-1: none)
   // reductions of a fused step whose second pass has not run yet: the next fused step
-  // folds them in its first workgroup, anything that reads results flushes them first
+  // folds them in its first workgroups, anything that reads results flushes them first
   bool pending = false;
   int pend_nb = 0, pend_buf = 0;
   int pend_mask = 1;               // bit k: step pend_step + k

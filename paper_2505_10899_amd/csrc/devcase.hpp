@@ -1,7 +1,6 @@
 // Device-side description of one case and the helpers every kernel shares:
 // pull streaming with bounce-back walls and storage decoding, fixed-order block
-// reductions, and the end-of-step "last block" that finishes the volume reductions
-// and advances the step counter.
+// reductions, and their second pass, which a later launch does.
 #pragma once
 #include <hip/hip_runtime.h>
 

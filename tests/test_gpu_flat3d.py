@@ -71,3 +71,19 @@ def test_one_step_and_reductions(size, storage, wall, visc, nl):
         for k, s in scale.items():
             assert float(np.max(np.abs(h[k][t] - obs[t][k]))) <= rtol * s * total, (t, k)
         assert not h["nonfinite"].any()
+
+
+@pytest.mark.parametrize("which", ["below_2GiB", "above_2GiB"])
+def test_the_march_either_side_of_the_buffer_limit(which, monkeypatch):
+    """FP16S columns step in two passes by default; the section march that set_tile chooses
+    still changes its form of access at arrays of 2 GiB."""
+    import test_gpu_max_size as M
+    from paper_2505_10899_amd import vclb
+
+    class March(vclb.Case):
+        def __init__(self, *a, **k):
+            super().__init__(*a, **k)
+            self.set_tile(32, 19, 8)
+
+    monkeypatch.setattr(vclb, "Case", March)
+    M.test_d3q19_fp16s_either_side_of_the_buffer_limit(which)
