@@ -1371,7 +1371,7 @@ struct vclb_batch {
   // exist if lx > 0, `lane` says which is in force
   bool lane = false;
   int lx = 0, ly = 0, ntiles = 0;
-  int2* d_tiles = nullptr;            // (case, tile) of every workgroup
+  int2* d_tiles = nullptr;            // (case, tile or its complement) of every workgroup
   int2* d_tile_cases = nullptr;       // (first tile, tile count) per case
 };
 
@@ -1798,11 +1798,8 @@ int vclb_batch_create(const vclb_params* cases, int32_t ncases, vclb_batch** out
   }
   e = hipMemcpy(b->d_cases, table.data(), table.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(b->d_reduce, chunks.data(), chunks.size() * sizeof(int2), hipMemcpyHostToDevice);
-  if (e == hipSuccess && b->lx > 0) {
-    e = hipMemcpy(b->d_tiles, tiles.data(), tiles.size() * sizeof(int2), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-      e = hipMemcpy(b->d_tile_cases, tile_cases.data(), tile_cases.size() * sizeof(int2), hipMemcpyHostToDevice);
-  }
+  if (e == hipSuccess && b->lx > 0)
+    e = hipMemcpy(b->d_tile_cases, tile_cases.data(), tile_cases.size() * sizeof(int2), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     vclb_batch_destroy(b);
     return hip_fail(e, "batch set-up");
@@ -1811,6 +1808,15 @@ int vclb_batch_create(const vclb_params* cases, int32_t ncases, vclb_batch** out
   if (rc) {
     vclb_batch_destroy(b);
     return rc;
+  }
+  if (b->lx > 0) {   // the tiles of cases that these runs do in bands are marked
+    for (int2& w : tiles)
+      if (b->items[size_t(b->case_items[size_t(w.x)].x)].y < 0) w.y = ~w.y;
+    e = hipMemcpy(b->d_tiles, tiles.data(), tiles.size() * sizeof(int2), hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+      vclb_batch_destroy(b);
+      return hip_fail(e, "batch set-up");
+    }
   }
   *out = b;
   return VCLB_OK;

@@ -70,7 +70,7 @@ int launch_batch_reduce(const void* cases, int ncases, const int2* blocks, int n
                         hipStream_t s);
 
 struct BatchArgs {
-  const int2* tiles;        // lane tiles: (case, tile) of every workgroup
+  const int2* tiles;        // lane tiles: (case, tile, or its complement: see k_batch_tile2d) of every workgroup
   int ntiles;
   const int4* items;        // (case, x0, y0, y1) of every work item, case-major; x0 < 0: a
                             // flattened band of rows [y0, y1), else a strip of columns from x0

@@ -76,6 +76,7 @@ __device__ __forceinline__ void stg_nt(T* p, unsigned i, T v) {
 // fold: the storage rounds coarsely enough that the phis entry a node writes for itself
 // absorbs the sum of the rounding errors of the deviations it wrote (rounding(v): stored
 // value minus v)
+// enc / dec: to and from the stored type; store_s: a value already of the stored type
 struct StoreF64 {
   using S = double;
   using R = double;
@@ -89,9 +90,13 @@ struct StoreF64 {
   template <class I>
   __device__ static void store(S* p, I i, R v) { stg(p, i, v); }
   template <class I>
+  __device__ static void store_s(S* p, I i, S v) { stg(p, i, v); }
+  template <class I>
   __device__ static R load_nt(const S* p, I i) { return ldg_nt(p, i); }
   template <class I>
   __device__ static void store_nt(S* p, I i, R v) { stg_nt(p, i, v); }
+  template <class I>
+  __device__ static void store_s_nt(S* p, I i, S v) { stg_nt(p, i, v); }
 };
 // FP32 storage uses the same deviation representation as FP16S (see below): the g
 // arithmetic then never rounds at the magnitude of the rest populations (~0.7), which
@@ -109,9 +114,13 @@ struct StoreF32 {
   template <class I>
   __device__ static void store(S* p, I i, R v) { stg(p, i, v); }
   template <class I>
+  __device__ static void store_s(S* p, I i, S v) { stg(p, i, v); }
+  template <class I>
   __device__ static R load_nt(const S* p, I i) { return ldg_nt(p, i); }
   template <class I>
   __device__ static void store_nt(S* p, I i, R v) { stg_nt(p, i, v); }
+  template <class I>
+  __device__ static void store_s_nt(S* p, I i, S v) { stg_nt(p, i, v); }
 };
 // FP16 storage of deviations from the rest equilibrium: g_i - phi r_i with
 // r_0 = 1 + (w_0 - 1) lambda, r_i = w_i lambda (g_eq at u = 0, mu = 0), where phi is that
@@ -141,6 +150,8 @@ struct StoreF16S {
     stg(reinterpret_cast<unsigned short*>(p), i, __half_as_ushort(__float2half_rn(v)));
   }
   template <class I>
+  __device__ static void store_s(S* p, I i, S v) { stg(reinterpret_cast<unsigned short*>(p), i, __half_as_ushort(v)); }
+  template <class I>
   __device__ static R load_nt(const S* p, I i) {
     return __half2float(__ushort_as_half(ldg_nt(reinterpret_cast<const unsigned short*>(p), i)));
   }
@@ -148,7 +159,19 @@ struct StoreF16S {
   __device__ static void store_nt(S* p, I i, R v) {
     stg_nt(reinterpret_cast<unsigned short*>(p), i, __half_as_ushort(__float2half_rn(v)));
   }
+  template <class I>
+  __device__ static void store_s_nt(S* p, I i, S v) {
+    stg_nt(reinterpret_cast<unsigned short*>(p), i, __half_as_ushort(v));
+  }
 };
+
+// v as rounded to its type: a conversion of the result does not merge with the multiply-add
+// that formed v (which would round once instead of twice)
+template <class R>
+__device__ __forceinline__ R rounded(R v) {
+  asm("" : "+v"(v));
+  return v;
+}
 
 // ---------------------------------------------------------------- per-case constants
 template <class L, class R>

@@ -46,7 +46,8 @@ __global__ void __launch_bounds__(tile2d_lanes(LX, LY, HELP))
     return;
   }
   const int tile = xcd_tile(int(blockIdx.x) - extra, ntiles);
-  tile2d_step<St, COUPLED, UNIT, VISC, LX, LY, HELP, NT>(c, c.t, tile, ntx, reduce ? c.part_w + tile : nullptr, ntiles);
+  tile2d_step<St, COUPLED, UNIT, VISC, LX, LY, HELP, NT, Once::Level>(c, c.t, tile, ntx,
+                                                                      reduce ? c.part_w + tile : nullptr, ntiles, false);
 }
 
 // Up to three steps in one launch (tile2d_multi).  As above, the first workgroups sum the
@@ -118,7 +119,7 @@ int launch_tile2d(const DevCase<D2Q9, St>& c, int lx, int ly, int reduce, hipStr
 }
 
 // One step of every case of a batch in lane tiles: workgroup i does tile tiles[i].y of case
-// tiles[i].x, after one workgroup per case that sums the previous step's partials.
+// tiles[i].x (the tile's complement for a case that runs would do in bands), after one workgroup per case that sums the previous step's partials.
 template <class St, bool UNIT, bool VISC, int LX, int LY, bool HELP>
 __global__ void __launch_bounds__(tile2d_lanes(LX, LY, HELP))
     k_batch_tile2d(const DevCase<D2Q9, St>* __restrict__ cases, BatchArgs a) {
@@ -130,8 +131,8 @@ __global__ void __launch_bounds__(tile2d_lanes(LX, LY, HELP))
   const int i = xcd_tile(int(blockIdx.x) - extra, a.ntiles);
   const int2 w = a.tiles[i];
   const DevCase<D2Q9, St>& c = cases[w.x];
-  tile2d_step<St, true, UNIT, VISC, LX, LY, HELP, false>(c, a.t, w.y, (c.nx + (1 << LX) - 1) >> LX,
-                                                         a.reduce ? a.part_w + i : nullptr, a.nitems);
+  tile2d_step<St, true, UNIT, VISC, LX, LY, HELP, false, Once::OfBand>(
+      c, a.t, w.y < 0 ? ~w.y : w.y, (c.nx + (1 << LX) - 1) >> LX, a.reduce ? a.part_w + i : nullptr, a.nitems, w.y < 0);
 }
 
 template <class St>

@@ -87,6 +87,34 @@ __device__ __forceinline__ void tile2d_sums(const Case& c, const PhiPsi* ring, i
   }
 }
 
+// f of a node just updated, on its way to the stored type.  In 2 bytes a value is rounded
+// either to 4 bytes first or once, together with the multiply-add that forms it.  Which of
+// the two is that of the march the case would otherwise run, so that its results are the
+// march's bit for bit: the compiled march of a single case rounds the directions that take
+// no wall term once (ONCE), a batch's strips none and its bands direction 0 (`band`).
+// e holds these directions encoded.
+enum class Once { Level, OfBand };
+template <Once ONCE>
+constexpr bool encoded_first(int i) { return D2Q9::cy[i] == 0 && (ONCE == Once::Level || i == 0); }
+template <class St, Once ONCE>
+__device__ __forceinline__ void encode_first(const typename St::R (&f)[9], bool band, typename St::S (&e)[4]) {
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    if (!encoded_first<ONCE>(i)) continue;
+    typename St::S a = St::enc(f[i]);
+    if constexpr (sizeof(typename St::S) == 2) {
+      unsigned u = __half_as_ushort(a);
+      asm("" : "+v"(u));   // on its own: not converted after the choice below
+      a = __ushort_as_half((unsigned short)u);
+      if (ONCE != Once::Level) {
+        const typename St::S b = St::enc(rounded(f[i]));   // both, with no branch (which would part the update)
+        a = band ? a : b;
+      }
+    }
+    e[i & 3] = a;
+  }
+}
+
 // One step (time level t) of tile `tile` of case c, by one whole workgroup; ntx tiles span
 // a row of tiles.  part: this tile's slot of the reduction partials (field j of label k at
 // [(k * 12 + j) * part_stride]), null when the step records none.
@@ -97,9 +125,11 @@ __device__ __forceinline__ void tile2d_sums(const Case& c, const PhiPsi* ring, i
 // free), but a wave in three idles; large grids, which need every wave
 // (1501 x 1003 FP16S: 27.7 -> 31.3 us), leave both to the tile's own lanes.
 // NT: stores of the populations and loads of f with the non-temporal hint.
-template <class St, bool COUPLED, bool UNIT, bool VISC, int LX, int LY, bool HELP, bool NT>
+// ONCE: the directions of f that may be rounded once: all on the level, or direction 0 of a
+// case that a batch's runs would do in bands (`band`).
+template <class St, bool COUPLED, bool UNIT, bool VISC, int LX, int LY, bool HELP, bool NT, Once ONCE>
 __device__ __forceinline__ void tile2d_step(const DevCase<D2Q9, St>& c, long t, int tile, int ntx,
-                                            double* __restrict__ part, long part_stride) {
+                                            double* __restrict__ part, long part_stride, bool band) {
   using L = D2Q9;
   using R = typename St::R;
   using S = typename St::S;
@@ -193,6 +223,17 @@ __device__ __forceinline__ void tile2d_step(const DevCase<D2Q9, St>& c, long t, 
     }
     NodeOut<L, R> out;
     node_update_d2q9<R, COUPLED, St::shifted, UNIT, VISC>(c.np, in, g, f, J, out);
+    auto store_f = [&](int i, S e) {
+      if constexpr (NT) St::store_s_nt(c.pop[1][dst] + long(i) * ns, nn, e);
+      else St::store_s(c.pop[1][dst] + long(i) * ns, nn, e);
+    };
+    if constexpr (COUPLED) {
+      S e[4];
+      encode_first<St, ONCE>(f, band, e);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (encoded_first<ONCE>(i)) store_f(i, e[i]);
+    }
     R res = R(0);   // rounding of the stored g deviations, taken off the stored phi
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
@@ -216,10 +257,8 @@ __device__ __forceinline__ void tile2d_step(const DevCase<D2Q9, St>& c, long t, 
           if (L::cy[i] > 0) f[i] += c.np.wt[i] * out.rho;
       }
 #pragma unroll
-      for (int i = 0; i < Q; ++i) {
-        if constexpr (NT) St::store_nt(c.pop[1][dst] + long(i) * ns, nn, f[i]);
-        else St::store(c.pop[1][dst] + long(i) * ns, nn, f[i]);
-      }
+      for (int i = 0; i < Q; ++i)
+        if (!encoded_first<ONCE>(i)) store_f(i, St::enc(f[i]));
     }
     stg(c.Jw, nn, J[0]);
     stg(c.Jw + ns, nn, J[1]);
@@ -356,6 +395,8 @@ __device__ __forceinline__ void tile2d_multi(const DevCase<D2Q9, St>& c, long t,
                                trig[0][RX + RY + n - 1 - m], in.u[0], in.u[1]);
       NodeOut<L, R> out;
       node_update_d2q9<R, COUPLED, St::shifted, UNIT, VISC>(c.np, in, g, f, J, out);
+      S e[4];
+      if constexpr (COUPLED) encode_first<St, Once::Level>(f, false, e);
       R res = R(0);   // rounding of the stored g deviations, taken off the stored phi
 #pragma unroll
       for (int i = 0; i < Q; ++i) {
@@ -376,19 +417,20 @@ __device__ __forceinline__ void tile2d_multi(const DevCase<D2Q9, St>& c, long t,
             if (L::cy[i] > 0) f[i] += c.np.wt[i] * out.rho;
         }
       }
+      auto stored_f = [&](int i) -> S { return encoded_first<Once::Level>(i) ? e[i & 3] : St::enc(f[i]); };
       const float own_phi = St::shifted ? float(in.nphi[0] - res) : 0.0f;
       if (m > 0) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
           pops[0][i][tid] = St::enc(g[i]);
-          if constexpr (COUPLED) pops[1][i][tid] = St::enc(f[i]);
+          if constexpr (COUPLED) pops[1][i][tid] = stored_f(i);
         }
         if constexpr (St::shifted) phl[tid] = own_phi;
       } else if (xg < nx && yg < ny) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
           St::store(c.pop[0][dst] + long(i) * ns, nn, g[i]);
-          if constexpr (COUPLED) St::store(c.pop[1][dst] + long(i) * ns, nn, f[i]);
+          if constexpr (COUPLED) St::store_s(c.pop[1][dst] + long(i) * ns, nn, stored_f(i));
         }
         stg(c.Jw, nn, J[0]);
         stg(c.Jw + ns, nn, J[1]);

@@ -1,0 +1,76 @@
+"""The forms of a step (row or section march, lane tiles, a batch's runs) of one case give the
+same state bit for bit, so that neither the library's choice of a form nor its autotuner
+changes results.  No tolerance: states are compared for equality."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+# a size per default shape of the lane tiles: 8 x 8 and 16 x 16 (three steps in a launch),
+# 16 x 8, 64 x 4, 128 x 4 plain and (rows of whole lines) with the non-temporal hint
+SIZES = [(66, 45), (251, 200), (333, 301), (801, 777), (2051, 1843), (2048, 1843)]
+
+
+def _case(nx, ny, storage, wall, visc=1.0, general=False, nl=1):
+    m = min(nx, ny)
+    c1, c2 = (0.31 * nx + 0.13, 0.47 * ny + 0.21, 0.0), (0.73 * nx + 0.07, 0.52 * ny + 0.11, 0.0)
+    p = W.CaseParams(nx=nx, ny=ny, storage=storage, wall_y=wall, rho_light=0.1, label_centres=[c1, c2][:nl])
+    if wall:
+        p = p.replace(wall_u_bottom=(-0.02, 0.0, 0.0), wall_u_top=(0.015, 0.0, 0.0), wall_cos_bottom=0.4,
+                      wall_cos_top=-0.3)
+    if visc != 1.0:
+        p = p.replace(nu_light=p.nu * visc)
+    if general:
+        p = p.replace(s_g=(0.0, 1.3, 1.2) + (0.0,) * 6, s_f=(0.0, 1.1, 1.25) + (0.0,) * 6)
+    phi0 = W.drops_phi(p, [(*c1, min(24.0, 0.19 * m)), (*c2, min(15.0, 0.1 * m))])
+    y, x = np.mgrid[0:ny, 0:nx]
+    u0 = 0.02 * np.stack([np.sin(2 * np.pi * y / ny), np.sin(2 * np.pi * x / nx)])[:, None]
+    if wall:
+        u0[1] = 0.0
+    return p, np.clip(phi0, 0.0, 1.0), u0
+
+
+def _states(p, phi0, u0, steps, tile=None):
+    from paper_2505_10899_amd import vclb as v
+    c = v.Case(p).init(phi0, u0)
+    if tile is not None:
+        c.set_tile(*tile)
+    c.step(steps)
+    return c.get_state()
+
+
+def _same(a, b):
+    for name, x, y in zip("gfJ", a, b):
+        assert (x is None) == (y is None)
+        assert x is None or np.array_equal(x, y), (name, float(np.abs(x - y).max()), float(np.mean(x != y)))
+
+
+@pytest.mark.parametrize("wall,visc,general", [(False, 1.0, False), (True, 3.75, False), (True, 1.0, True),
+                                               (False, 3.75, True)])
+@pytest.mark.parametrize("nx,ny", SIZES)
+@pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s"])
+def test_lane_tiles_equal_the_march(nx, ny, storage, wall, visc, general):
+    print("case:", nx, ny, storage, wall, visc, general, flush=True)
+    args = _case(nx, ny, storage, wall, visc, general, nl=2 if general else 1)
+    _same(_states(*args, 10), _states(*args, 10, tile=(64, 16)))
+
+
+@pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s"])
+def test_batch_lane_tiles_equal_the_runs(storage):
+    """Cases that the runs do in bands (narrow against a run's 512 lanes) and in strips."""
+    from paper_2505_10899_amd import vclb as v
+    sizes = [(130, 67), (64, 64), (300, 90), (512, 40), (70, 333), (1024, 30), (48, 48), (150, 300)]
+    sims = [_case(nx, ny, storage, k % 2 == 1) for k, (nx, ny) in enumerate(sizes)]
+    got = []
+    for runs in (False, True):
+        b = v.Batch([p for p, _, _ in sims])
+        b.init([(phi, u) for _, phi, u in sims])
+        if runs:
+            b.set_tile(*b.tile()[:2])   # the default run shape
+        b.step(10)
+        got.append([c.get_state() for c in b.cases])
+    for k, (x, y) in enumerate(zip(*got)):
+        print("case:", sizes[k], storage, flush=True)
+        _same(x, y)
