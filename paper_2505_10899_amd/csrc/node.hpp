@@ -280,6 +280,12 @@ __device__ __forceinline__ R stress_rate(const NodeParams<L, R>& p, R phi, R irh
   return recip(R(0.5) + R(3) * (p.mu_l + phi * p.dmu) * irho);
 }
 
+template <class R>
+__device__ __forceinline__ R fma_of(R a, R b, R c) {
+  if constexpr (sizeof(R) == 4) return __builtin_fmaf(a, b, c);
+  else return __builtin_fma(a, b, c);
+}
+
 // ---------------------------------------------------------------- D2Q9 in closed form
 // m = M g with the shared partial sums of the rows of Eq. 24
 template <class R>
@@ -332,7 +338,10 @@ __device__ __forceinline__ void d2q9_from_moments(const R (&m)[9], R (&v)[9]) {
 // formed.
 // VISC: the two phases have different viscosities; the stress rows relax at the node's
 // own 1 / tau_f (Eq. 27), see stress_rate.
-template <class R, bool COUPLED, bool SH, bool UNIT = false, bool VISC = false>
+// MARCH: a sum of two products whose fused one the compiler is free to choose, V of Eq. 32, is
+// spelled out as the row march's compiled form has it (for kernels that it would compile the
+// other way: they then give the march's results bit for bit).
+template <class R, bool COUPLED, bool SH, bool UNIT = false, bool VISC = false, bool MARCH = false>
 __device__ __forceinline__ void node_update_d2q9(const NodeParams<D2Q9, R>& p, const NodeIn<D2Q9, R>& in,
                                                  R (&g)[9], R (&f)[9], R (&J)[2], NodeOut<D2Q9, R>& out) {
   const R* q = in.nphi;
@@ -374,7 +383,8 @@ __device__ __forceinline__ void node_update_d2q9(const NodeParams<D2Q9, R>& p, c
   J[0] = Jx;
   J[1] = Jy;
   const R inv = rsqrt_of(gsx * gsx + gsy * gsy + p.eps2);
-  const R Vx = R(3) * dJx + An * (gsx * inv), Vy = R(3) * dJy + An * (gsy * inv);  // Eq. 32: G_i = w_i c_i . V
+  const R Vx = MARCH ? fma_of(An, gsx * inv, R(3) * dJx) : R(3) * dJx + An * (gsx * inv);   // Eq. 32: G_i = w_i c_i . V
+  const R Vy = MARCH ? fma_of(An, gsy * inv, R(3) * dJy) : R(3) * dJy + An * (gsy * inv);
   // g (Eq. 33): equilibrium moments (phi, -4 phi + 2H, 4 phi - 3H, Jx, -Jx, Jy, -Jy, 0, 0), H = mu + lambda phi;
   // in deviation variables (subtract M r phi) they are (0, 2 mu, -3 mu, Jx, -Jx, Jy, -Jy, 0, 0).
   // source moments (0, 0, 0, Vx/3, -Vx/3, Vy/3, -Vy/3, 0, 0).

@@ -222,7 +222,7 @@ __device__ __forceinline__ void tile2d_step(const DevCase<D2Q9, St>& c, long t, 
                              in.u[0], in.u[1]);
     }
     NodeOut<L, R> out;
-    node_update_d2q9<R, COUPLED, St::shifted, UNIT, VISC>(c.np, in, g, f, J, out);
+    node_update_d2q9<R, COUPLED, St::shifted, UNIT, VISC, !COUPLED>(c.np, in, g, f, J, out);
     auto store_f = [&](int i, S e) {
       if constexpr (NT) St::store_s_nt(c.pop[1][dst] + long(i) * ns, nn, e);
       else St::store_s(c.pop[1][dst] + long(i) * ns, nn, e);
@@ -394,7 +394,7 @@ __device__ __forceinline__ void tile2d_multi(const DevCase<D2Q9, St>& c, long t,
         vortex_from_factors<R>(c.np.U0, trig[0][rx], trig[1][rx], trig[0][RX + ry], trig[1][RX + ry],
                                trig[0][RX + RY + n - 1 - m], in.u[0], in.u[1]);
       NodeOut<L, R> out;
-      node_update_d2q9<R, COUPLED, St::shifted, UNIT, VISC>(c.np, in, g, f, J, out);
+      node_update_d2q9<R, COUPLED, St::shifted, UNIT, VISC, !COUPLED>(c.np, in, g, f, J, out);
       S e[4];
       if constexpr (COUPLED) encode_first<St, Once::Level>(f, false, e);
       R res = R(0);   // rounding of the stored g deviations, taken off the stored phi

@@ -13,10 +13,12 @@ pytestmark = pytest.mark.gpu
 SIZES = [(66, 45), (251, 200), (333, 301), (801, 777), (2051, 1843), (2048, 1843)]
 
 
-def _case(nx, ny, storage, wall, visc=1.0, general=False, nl=1):
+def _case(nx, ny, storage, wall, visc=1.0, general=False, nl=1, mode="coupled"):
     m = min(nx, ny)
     c1, c2 = (0.31 * nx + 0.13, 0.47 * ny + 0.21, 0.0), (0.73 * nx + 0.07, 0.52 * ny + 0.11, 0.0)
-    p = W.CaseParams(nx=nx, ny=ny, storage=storage, wall_y=wall, rho_light=0.1, label_centres=[c1, c2][:nl])
+    p = W.CaseParams(nx=nx, ny=ny, storage=storage, wall_y=wall, rho_light=0.1, label_centres=[c1, c2][:nl], mode=mode)
+    if mode == "vortex":
+        p = p.replace(U0=0.04, T=400.0, mobility=0.02)
     if wall:
         p = p.replace(wall_u_bottom=(-0.02, 0.0, 0.0), wall_u_top=(0.015, 0.0, 0.0), wall_cos_bottom=0.4,
                       wall_cos_top=-0.3)
@@ -55,6 +57,15 @@ def test_lane_tiles_equal_the_march(nx, ny, storage, wall, visc, general):
     print("case:", nx, ny, storage, wall, visc, general, flush=True)
     args = _case(nx, ny, storage, wall, visc, general, nl=2 if general else 1)
     _same(_states(*args, 10), _states(*args, 10, tile=(64, 16)))
+
+
+@pytest.mark.parametrize("nx,ny", SIZES)
+@pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s"])
+def test_lane_tiles_equal_the_march_vortex(nx, ny, storage):
+    print("case:", nx, ny, storage, flush=True)
+    for general in (False, True):
+        p, phi0, _ = _case(nx, ny, storage, False, general=general, mode="vortex")
+        _same(_states(p, phi0, None, 10), _states(p, phi0, None, 10, tile=(64, 16)))
 
 
 @pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s"])
