@@ -137,7 +137,12 @@ __global__ void __launch_bounds__(kBlock, (sizeof(typename St::R) == 8 ? 3 : 4))
   });
   (void)phi_of_pulled<L, St>(g, ps, c.np.rest);
   NodeOut<L, R> out;
-  node_update_mom_s<L, R, true, St::shifted, UNIT, VISC>(c.np, st, g, f, J, out);
+  node_update_mom_s<L, R, true, St::shifted, UNIT, VISC, true>(c.np, st, g, f, J, out);
+  // with walls the march converts f behind the wall terms' branches, formed before them
+  if constexpr (WALL && sizeof(typename St::S) == 2) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) f[i] = formed(f[i]);
+  }
   R res = R(0);   // rounding of the stored g deviations, taken off the stored phi
 #pragma unroll
   for (int i = 0; i < Q; ++i) {

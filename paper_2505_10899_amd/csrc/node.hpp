@@ -173,6 +173,14 @@ __device__ __forceinline__ R rounded(R v) {
   return v;
 }
 
+// The same, and v is formed at this place: not at its use in another block, away from the
+// products of the sum that it is.
+template <class R>
+__device__ __forceinline__ R formed(R v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // ---------------------------------------------------------------- per-case constants
 template <class L, class R>
 struct NodeParams {
@@ -597,7 +605,9 @@ struct StencilOut {
 // UNIT: every rate outside the g flux rows and the f stress rows is exactly 1 (the
 // defaults); those rows then relax straight to m_eq + src / 2 without forming m.
 // VISC: the stress rows relax at the node's own rate (stress_rate).
-template <class L, class R, bool COUPLED, bool SH, bool UNIT = false, bool VISC = false>
+// MARCH: sums of two products whose fused one the compiler is free to choose are spelled out
+// as the section march's compiled form has them, see node_update_d2q9.
+template <class L, class R, bool COUPLED, bool SH, bool UNIT = false, bool VISC = false, bool MARCH = false>
 __device__ __forceinline__ void node_update_mom_s(const NodeParams<L, R>& p, const StencilOut<L, R>& st,
                                                   R (&g)[L::Q], R (&f)[L::Q], R (&J)[L::D], NodeOut<L, R>& out) {
   constexpr int Q = L::Q, D = L::D;
@@ -652,7 +662,9 @@ __device__ __forceinline__ void node_update_mom_s(const NodeParams<L, R>& p, con
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     Jn[d] = phi * u[d];
-    V[d] = R(3) * (Jn[d] - J[d]) + An * (gpsi[d] * inv);
+    if constexpr (!MARCH) V[d] = R(3) * (Jn[d] - J[d]) + An * (gpsi[d] * inv);
+    else if constexpr (sizeof(R) == 8) V[d] = fma_of(R(3), Jn[d] - J[d], An * (gpsi[d] * inv));
+    else V[d] = fma_of(An, gpsi[d] * inv, R(3) * (Jn[d] - J[d]));
     J[d] = Jn[d];
   }
   // g (Eq. 33) in moment space; with SH the equilibrium enters as g_eq - r phi and the
@@ -694,8 +706,15 @@ __device__ __forceinline__ void node_update_mom_s(const NodeParams<L, R>& p, con
       constexpr int k = decltype(K)::value;
       constexpr double w0 = mom_w<L>(k);
       constexpr double rest = double(L::M[k][0]);
-      const R eq = R(3.0 * (w0 - rest)) * press +
-                   rho * (R(3) * mom_lin<L, R, k>(u) + R(4.5) * mom_quad<L, R, k>(u, u) - R(1.5 * w0) * uu);
+      R eq;
+      constexpr double wp = 3.0 * (w0 - rest);
+      if constexpr (MARCH && wp > 1e-6) {
+        const R ru = R(3) * mom_lin<L, R, k>(u) + R(4.5) * mom_quad<L, R, k>(u, u) - R(1.5 * w0) * uu;
+        eq = fma_of(R(wp), press, rho * ru);
+      } else {
+        eq = R(3.0 * (w0 - rest)) * press +
+             rho * (R(3) * mom_lin<L, R, k>(u) + R(4.5) * mom_quad<L, R, k>(u, u) - R(1.5 * w0) * uu);
+      }
       const R src = R(3) * mom_lin<L, R, k>(Fs) + R(3) * mom_quad<L, R, k>(u, grho);
       if constexpr (UNIT && !FRateRows<L>::need(k)) {
         fm[k] = eq + R(0.5) * src;

@@ -68,6 +68,30 @@ def test_lane_tiles_equal_the_march_vortex(nx, ny, storage):
         _same(_states(p, phi0, None, 10), _states(p, phi0, None, 10, tile=(64, 16)))
 
 
+@pytest.mark.parametrize("wall,visc,general", [(False, 1.0, False), (True, 3.75, False), (True, 1.0, True),
+                                               (False, 3.75, True)])
+@pytest.mark.parametrize("nx,ny,nz", [(36, 30, 40), (61, 45, 130), (64, 16, 24)])
+@pytest.mark.parametrize("storage", ["fp64", "fp16s"])
+def test_two_passes_equal_the_march(nx, ny, nz, storage, wall, visc, general):
+    """(In FP32 the two forms agree to rounding only: see test_gpu_flat3d.py.)"""
+    print("case:", nx, ny, nz, storage, wall, visc, general, flush=True)
+    c1 = (0.47 * nx + 0.13, 0.52 * ny + 0.21, 0.0)
+    p = W.CaseParams(lattice="D3Q19", nx=nx, ny=ny, nz=nz, storage=storage, sigma=0.005, nu=0.05, rho_light=0.1,
+                     wall_y=wall, label_centres=[c1])
+    if wall:
+        p = p.replace(wall_u_bottom=(-0.01, 0.0, 0.0), wall_u_top=(0.01, 0.0, 0.005), wall_cos_bottom=0.4,
+                      wall_cos_top=-0.3)
+    if visc != 1.0:
+        p = p.replace(nu_light=p.nu * visc)
+    if general:
+        p = p.replace(s_g=(0.0, 1.3, 1.2) + (0.0,) * 16, s_f=(0.0, 1.1, 1.25) + (0.0,) * 16)
+    z, y, x = np.mgrid[0:nz, 0:ny, 0:nx]
+    R = min(nx, ny) / 5.0 * (1.0 + 0.1 * np.cos(2 * np.pi * z / nz))
+    phi0 = 0.5 + 0.5 * np.tanh(2.0 * (R - np.hypot(x - c1[0], y - c1[1])) / p.W)
+    u0 = 0.02 * np.stack([np.sin(2 * np.pi * y / ny), np.zeros(x.shape), np.cos(2 * np.pi * x / nx)])
+    _same(_states(p, phi0, u0, 6), _states(p, phi0, u0, 6, tile=(32, 8, 8)))
+
+
 @pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s"])
 def test_batch_lane_tiles_equal_the_runs(storage):
     """Cases that the runs do in bands (narrow against a run's 512 lanes) and in strips."""
