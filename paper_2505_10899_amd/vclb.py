@@ -134,7 +134,7 @@ SEED_FIELDS = 10
 NORMAL_TAU = 0.3   # the unit normal is differentiated where |grad psi| >= NORMAL_TAU
 
 
-VERSION = 20100   # VCLB_VERSION of include/vclb.h, whose struct layouts Params and Obs mirror
+VERSION = 20200   # VCLB_VERSION of include/vclb.h, whose struct layouts and entry points this file mirrors
 
 
 def lib():
@@ -144,13 +144,15 @@ def lib():
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2505_10899_amd.build`")
         L = ctypes.CDLL(LIB_PATH)
+        L.vclb_version.restype = ctypes.c_int
+        have = L.vclb_version()
+        if have // 10000 != VERSION // 10000 or have < VERSION:
+            raise ImportError(f"{LIB_PATH} has version {have}, this binding needs {VERSION} (its parameter layout and "
+                              "entry points): rebuild it with `python -m paper_2505_10899_amd.build`")
         for name, res, args in _SIGS:
             fn = getattr(L, name)
             fn.restype = res
             fn.argtypes = args
-        if L.vclb_version() // 10000 != VERSION // 10000:
-            raise ImportError(f"{LIB_PATH} has version {L.vclb_version()}, this binding needs {VERSION} (its "
-                              "parameter layout): rebuild it with `python -m paper_2505_10899_amd.build`")
         _lib = L
     return _lib
 
