@@ -316,7 +316,7 @@ def run_single(name: str, storage: str, steps: int, warmup: int, tune: bool = Tr
     return {"nodes": p.n_nodes, "MLUPS": round(p.n_nodes / (ms * 1e-3) / 1e6, 1), "ms_per_step": round(ms, 4),
             "achieved_GBs": round(gbs, 1), "frac_hbm_peak": round(gbs / HBM_PEAK_GBS, 4),
             "bytes_per_node": bpn, "layout_bytes_per_node": layout_bytes(p.lattice, p.mode == "coupled", storage),
-            "tile": list(c.tile())}
+            "tile": list(c.tile()), "form": list(c.form())}
 
 
 # ----------------------------------------------------------------------------- CPU oracle

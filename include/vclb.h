@@ -166,10 +166,10 @@ const char* vclb_strerror(int code);
 const char* vclb_last_error(void);
 /* Version of this header as MAJOR * 10000 + MINOR * 100 + PATCH.  The major part changes
    with the layout of vclb_params or of any other struct here, the minor part with each set
-   of new entry points (2.2: vclb_adjoint_set_store); a library built from this header
+   of new entry points (2.2: vclb_adjoint_set_store; 2.3: vclb_case_get_form, _set_form); a library built from this header
    returns the same value from vclb_version, and a caller should refuse a library whose
    major part differs or whose version is lower. */
-#define VCLB_VERSION 20200
+#define VCLB_VERSION 20300
 /* Version of the library as MAJOR * 10000 + MINOR * 100 + PATCH (VCLB_VERSION of the
    header it was built from). */
 int vclb_version(void);
@@ -213,7 +213,7 @@ void vclb_case_destroy(vclb_case* c);
    waiting for its row round trips steps in tiles of one lane per node instead (the smallest
    three steps per launch), and a D3Q19 case whose rows or size do not suit the march, or
    with FP16S storage, in two passes in stored order; get_tile returns the march's shape all
-   the same, and set_tile chooses the march.  D2Q9: bx lanes (x columns; a multiple of 64 in
+   the same, and set_tile chooses the march (get_form says which runs, set_form goes back).  D2Q9: bx lanes (x columns; a multiple of 64 in
    64..256, or 512 or 1024 with FP32 or FP16S storage) marching ty >= 1 rows of y (by3
    ignored).  D3Q19: a bx x by3 section of (x, y)
    columns (bx * by3 a multiple of 64, at most 256, or at most 768 with FP32 or FP16S
@@ -222,6 +222,22 @@ void vclb_case_destroy(vclb_case* c);
    for shapes outside these limits. */
 int vclb_case_set_tile(vclb_case* c, int32_t bx, int32_t ty, int32_t by3);
 int vclb_case_get_tile(const vclb_case* c, int32_t* bx, int32_t* ty, int32_t* by3);
+
+/* The form the fused step runs in: the march in the shape of get_tile, tiles of w x h nodes
+   with one lane per node (D2Q9: 16 x 8, 64 x 4, 128 x 4, or 8 x 8 and 16 x 16, which take
+   three steps per launch), or two passes (D3Q19).  w and h are 0 unless in lane tiles.
+   set_form leaves the march's shape as it is, so set_tile(get_tile) and then
+   set_form(get_form) restore what runs.  VCLB_EINVAL for a form the case does not have: the
+   other lattice's, lane tiles beyond 2^26 nodes or with more tiles than the workspace holds
+   partial sums for, three steps per launch beyond 2^16 nodes, for a case of a batch or with
+   the global volume correction (16 x 16 also for coupled FP64), two passes from 2^28 nodes on.
+   The state does not depend on the form, bit for bit; but D3Q19 in FP32 the march and the two
+   passes agree to rounding. */
+#define VCLB_FORM_MARCH      0
+#define VCLB_FORM_LANE_TILES 1
+#define VCLB_FORM_TWO_PASSES 2
+int vclb_case_get_form(const vclb_case* c, int32_t* form, int32_t* w, int32_t* h);
+int vclb_case_set_form(vclb_case* c, int32_t form, int32_t w, int32_t h);
 
 /* Pick the tile of the fused step by timing `steps` steps of each candidate on the
    current state (saved and restored, as are the step counter and the recorded history),

@@ -404,6 +404,15 @@ int flush_pending(vclb_case* c, hipStream_t s) {
   return rc ? fail(VCLB_EHIP, "finalize launch failed") : VCLB_OK;
 }
 
+// Whether case c may step in lane tiles of t's shape: one the kernels have, within their
+// 32-bit byte offsets (three planes of 8 bytes), with room for the tiles' partial reductions,
+// and for three steps in a launch a second J (not in a batch's cases).
+constexpr long kLaneNodes = 1L << 26;
+bool lane_tile_ok(const vclb_case& c, const vclb::Tile& t) {
+  return c.p.lattice == VCLB_D2Q9 && vclb::tile2d_shape_ok(t.lx, t.ly) && long(c.p.nx) * c.p.ny <= kLaneNodes &&
+         tile2d_fits(c.p, t) && (!vclb::tile2d_multi_ok(t.lx, t.ly) || c.lay.J[0] != c.lay.J[1]);
+}
+
 // Whether a 2D case steps with one lane per node (tile2d.hip) or as a row march, and in
 // which tile.  Measured on square and oblong grids of 66 x 24 to 4096 x 4096, coupled and
 // vortex, each storage (us a step, march / tile):
@@ -427,7 +436,7 @@ void tile2d_choose(const vclb_params& p, vclb::Tile& t, bool multi) {
   const long n = long(p.nx) * p.ny;
   const size_t sb = storage_bytes(p.storage);
   const bool coupled = p.mode == VCLB_COUPLED;
-  if (n > (1L << 26)) return;
+  if (n > kLaneNodes) return;
   const bool lines = size_t(p.nx) * sb % 128 == 0;
   if (p.storage != VCLB_FP64 && n >= (1L << 23) && !(p.storage == VCLB_FP32 && coupled && !lines)) return;
   const size_t sets = size_t(n) * 9 * sb * (coupled ? 4 : 2);
@@ -441,15 +450,20 @@ void tile2d_choose(const vclb_params& p, vclb::Tile& t, bool multi) {
   if (tile2d_fits(p, u)) t = u;
 }
 
+// whether a 3D case may step in two passes: beyond, the 32-bit byte offsets of the pairs end
+// (16 bytes in FP64)
+bool two_passes_ok(const vclb_params& p) {
+  return p.lattice == VCLB_D3Q19 && long(p.nx) * p.ny * p.nz <= (1L << 28) - 1;
+}
+
 // Whether a 3D case steps in two passes in stored order (flat3d.hip) or as a section march.
 // The march wins where its sections and rows fit: from 2^21 nodes on, rows that start on
 // cache lines, 4- or 8-byte storage (96 x 96 x 384 FP32 263 / 296 us a step, FP64 505 / 566;
 // 64 x 64 x 300 FP32 115 / 102).  FP16S moves few enough bytes that the second reading of g
-// costs little (96 x 96 x 384 200 / 202, 128 x 128 x 200 240 / 184).  Beyond 2^28 nodes the
-// 32-bit byte offsets of the pairs end (16 bytes in FP64).
+// costs little (96 x 96 x 384 200 / 202, 128 x 128 x 200 240 / 184).
 bool flat3d_chosen(const vclb_params& p) {
   const long n = long(p.nx) * p.ny * p.nz;
-  if (n > (1L << 28) - 1) return false;
+  if (!two_passes_ok(p)) return false;
   const bool lines = size_t(p.nx) * storage_bytes(p.storage) % 128 == 0;
   return !(p.storage != VCLB_FP16S && lines && n >= (1L << 21));
 }
@@ -680,6 +694,36 @@ int vclb_case_get_tile(const vclb_case* c, int32_t* bx, int32_t* ty, int32_t* by
   return VCLB_OK;
 }
 
+int vclb_case_get_form(const vclb_case* c, int32_t* form, int32_t* w, int32_t* h) {
+  if (!c || !form || !w || !h) return fail(VCLB_EINVAL, "NULL argument");
+  const bool lane = c->tile.lx > 0;
+  *form = lane ? VCLB_FORM_LANE_TILES : (c->tile.flat ? VCLB_FORM_TWO_PASSES : VCLB_FORM_MARCH);
+  *w = lane ? 1 << c->tile.lx : 0;
+  *h = lane ? 1 << c->tile.ly : 0;
+  return VCLB_OK;
+}
+
+int vclb_case_set_form(vclb_case* c, int32_t form, int32_t w, int32_t h) {
+  if (!c) return fail(VCLB_EINVAL, "case is NULL");
+  vclb::Tile t = c->tile;
+  t.lx = t.ly = 0;
+  t.flat = false;
+  if (form == VCLB_FORM_LANE_TILES) {
+    for (int k = 1; k < 8; ++k) {
+      if (w == 1 << k) t.lx = k;
+      if (h == 1 << k) t.ly = k;
+    }
+    if (!lane_tile_ok(*c, t)) return fail(VCLB_EINVAL, "no lane tiles of this shape for this case");
+  } else if (form == VCLB_FORM_TWO_PASSES) {
+    t.flat = true;
+    if (!two_passes_ok(c->p)) return fail(VCLB_EINVAL, "the two passes cover D3Q19 cases below 2^28 nodes");
+  } else if (form != VCLB_FORM_MARCH) {
+    return fail(VCLB_EINVAL, "bad form");
+  }
+  c->tile = t;
+  return VCLB_OK;
+}
+
 int vclb_case_set_reduce_every(vclb_case* c, int32_t every) {
   if (!c || every < 0) return fail(VCLB_EINVAL, "bad reduce_every");
   c->reduce_every = every;
@@ -899,7 +943,6 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
   if (!c || steps < 1) return fail(VCLB_EINVAL, "bad autotune arguments");
   if (!c->inited) return fail(VCLB_ESTATE, "autotune needs an initialised case (its state is restored)");
   const vclb_params& p = c->p;
-  const bool alone = c->lay.J[0] != c->lay.J[1];   // may take several steps in a launch
   const std::string desc = "case:" + std::to_string(p.lattice) + ":" + std::to_string(p.storage) + ":" +
                            std::to_string(p.mode) + ":" + std::to_string(p.nx) + "x" + std::to_string(p.ny) + "x" +
                            std::to_string(p.nz) + (wall_y(p) ? "w" : "p") + std::to_string(std::max(1, p.nlabels));
@@ -931,9 +974,7 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
         vclb::Tile t = c->tile;
         t.lx = lx;
         t.ly = ly;
-        if (!rc && p.lattice == VCLB_D2Q9 && vclb::tile2d_shape_ok(lx, ly) && long(p.nx) * p.ny <= (1L << 26) &&
-            tile2d_fits(p, t) && (!vclb::tile2d_multi_ok(lx, ly) || alone))
-          c->tile = t;
+        if (!rc && lane_tile_ok(*c, t)) c->tile = t;
         if (!rc && flat && p.lattice == VCLB_D3Q19 && default_tile(p, 256).flat) c->tile.flat = true;
         return rc;
       }
@@ -948,11 +989,10 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
     const vclb::Tile def = default_tile(p, 256);
     if (def.lx > 0)
       for (const auto& sh : {std::pair<int, int>{3, 3}, {4, 4}, {4, 3}, {6, 2}, {7, 2}}) {
-        if (vclb::tile2d_multi_ok(sh.first, sh.second) && !alone) continue;
         vclb::Tile t = def;
         t.lx = sh.first;
         t.ly = sh.second;
-        if (tile2d_fits(p, t)) cands.push_back(t);
+        if (lane_tile_ok(*c, t)) cands.push_back(t);
       }
     for (int bx : {64, 128, 256, 512, 1024}) {
       if (bx > 256 && c->p.storage == VCLB_FP64) continue;

@@ -76,6 +76,8 @@ _SIGS = [
     ("vclb_case_destroy", None, [ctypes.c_void_p]),
     ("vclb_case_set_tile", ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]),
     ("vclb_case_get_tile", ctypes.c_int, [ctypes.c_void_p, _P(ctypes.c_int32), _P(ctypes.c_int32), _P(ctypes.c_int32)]),
+    ("vclb_case_get_form", ctypes.c_int, [ctypes.c_void_p, _P(ctypes.c_int32), _P(ctypes.c_int32), _P(ctypes.c_int32)]),
+    ("vclb_case_set_form", ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]),
     ("vclb_case_init", ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p]),
     ("vclb_case_set_state", ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p,
                                            ctypes.c_int64, ctypes.c_int, ctypes.c_void_p]),
@@ -129,12 +131,13 @@ _SIGS = [
                                         ctypes.c_int, _P(ctypes.c_double), ctypes.c_void_p]),
 ]
 
+FORMS = ("march", "lane_tiles", "two_passes")   # VCLB_FORM_*
 DERIVED = ("volume", "centroid_x", "centroid_y", "centroid_z", "D")
 SEED_FIELDS = 10
 NORMAL_TAU = 0.3   # the unit normal is differentiated where |grad psi| >= NORMAL_TAU
 
 
-VERSION = 20200   # VCLB_VERSION of include/vclb.h, whose struct layouts and entry points this file mirrors
+VERSION = 20300   # VCLB_VERSION of include/vclb.h, whose struct layouts and entry points this file mirrors
 
 
 def lib():
@@ -260,9 +263,22 @@ class Case:
         check(lib().vclb_case_get_tile(self.h, ctypes.byref(a), ctypes.byref(b), ctypes.byref(c)))
         return a.value, b.value, c.value
 
+    def form(self):
+        """What the fused step runs in: ("march", 0, 0), in the shape of tile(), ("lane_tiles",
+        w, h) or ("two_passes", 0, 0)."""
+        f, w, h = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
+        check(lib().vclb_case_get_form(self.h, ctypes.byref(f), ctypes.byref(w), ctypes.byref(h)))
+        return FORMS[f.value], w.value, h.value
+
+    def set_form(self, form: str, w: int = 0, h: int = 0):
+        """Choose a form of form(); set_tile chooses the march."""
+        if form not in FORMS:
+            raise VclbError(VCLB_EINVAL, f"form must be one of {FORMS}")
+        check(lib().vclb_case_set_form(self.h, FORMS.index(form), int(w), int(h)))
+
     def autotune(self, cache_path=None, steps: int = 5, stream=None):
         """Time the candidate tiles on the current state (restored afterwards) and keep the
-        fastest; returns (bx, ty, by3)."""
+        fastest; returns (bx, ty, by3), the march's shape: form() says what was chosen."""
         path = cache_path.encode() if cache_path else None
         check(lib().vclb_case_autotune(self.h, path, int(steps), _stream_handle(stream)))
         return self.tile()

@@ -109,3 +109,64 @@ def test_batch_lane_tiles_equal_the_runs(storage):
     for k, (x, y) in enumerate(zip(*got)):
         print("case:", sizes[k], storage, flush=True)
         _same(x, y)
+
+
+LANE_SHAPES = [(8, 8), (16, 16), (16, 8), (64, 4), (128, 4)]
+
+
+@pytest.mark.parametrize("mode,wall,visc,general", [("coupled", False, 1.0, False), ("coupled", True, 3.75, True),
+                                                    ("vortex", False, 1.0, False), ("vortex", False, 1.0, True)])
+@pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s"])
+def test_every_form_of_a_case(storage, mode, wall, visc, general):
+    """Every tile shape and march that the autotuner chooses from, chosen by name."""
+    from paper_2505_10899_amd import vclb as v
+    p, phi0, u0 = _case(133, 70, storage, wall, visc, general, nl=2, mode=mode)
+    u0 = u0 if mode == "coupled" else None
+    ref = _states(p, phi0, u0, 11, tile=(64, 16))
+    shapes = [s for s in LANE_SHAPES if s != (16, 16) or mode == "vortex" or storage != "fp64"]
+    tiles = [(64, 8), (128, 32), (256, 64)] + ([(512, 16), (1024, 8)] if storage != "fp64" else [])
+    for form in [("lane_tiles", *s) for s in shapes] + tiles:
+        print("case:", storage, mode, wall, visc, general, form, flush=True)
+        c = v.Case(p).init(phi0, u0)
+        if form[0] == "lane_tiles":
+            c.set_form(*form)
+            assert c.form() == form
+        else:
+            c.set_tile(*form)
+            assert c.form() == ("march", 0, 0) and c.tile()[:2] == form
+        c.step(11)
+        _same(c.get_state(), ref)
+
+
+def test_form_is_read_and_restored():
+    from paper_2505_10899_amd import vclb as v
+    p, phi0, u0 = _case(66, 45, "fp32", False)
+    c = v.Case(p).init(phi0, u0)
+    tile, form = c.tile(), c.form()
+    assert form == ("lane_tiles", 8, 8)
+    c.set_tile(*tile)
+    assert c.form() == ("march", 0, 0) and c.tile() == tile
+    c.step(2)
+    c.set_form(*form)
+    assert c.form() == form and c.tile() == tile
+    c.step(4)
+    _same(c.get_state(), _states(p, phi0, u0, 6))
+    for bad in [("two_passes",), ("lane_tiles", 8, 4), ("lane_tiles", 0, 0), ("lane_tiles", 2, 2), ("lane_tiles", 128, 8)]:
+        with pytest.raises(v.VclbError) as e:
+            c.set_form(*bad)
+        assert e.value.code == v.VCLB_EINVAL
+    # three steps per launch need room that a case of a batch, and a large one, do not have
+    big = v.Case(p.replace(nx=300, ny=300, label_centres=[]))
+    view = v.Batch([p]).cases[0]
+    coupled64 = v.Case(p.replace(storage="fp64"))
+    for case, shape in ((big, (8, 8)), (view, (8, 8)), (coupled64, (16, 16))):
+        with pytest.raises(v.VclbError):
+            case.set_form("lane_tiles", *shape)
+    p3 = W.CaseParams(lattice="D3Q19", nx=32, ny=16, nz=12, storage="fp64")
+    c3 = v.Case(p3)
+    assert c3.form() == ("two_passes", 0, 0)
+    c3.set_form("march")
+    assert c3.form() == ("march", 0, 0)
+    c3.set_form("two_passes")
+    with pytest.raises(v.VclbError):
+        c3.set_form("lane_tiles", 16, 8)
