@@ -242,8 +242,8 @@ int vclb_case_set_form(vclb_case* c, int32_t form, int32_t w, int32_t h);
 /* Pick the tile of the fused step by timing `steps` steps of each candidate on the
    current state (saved and restored, as are the step counter and the recorded history),
    or take it from the JSON-lines file cache_path when that holds an entry for this case's
-   lattice, storage, mode, shape, boundary and label count; a measured choice is appended
-   to cache_path (NULL: no file).  D2Q9 candidates: bx in {64, 128, 256} (and 512, 1024
+   lattice, storage, mode, shape, boundary and label count (entries of versions that did not
+   time every form are passed over); a measured choice is appended to cache_path (NULL: no file).  D2Q9 candidates: bx in {64, 128, 256} (and 512, 1024
    with 4-byte storage) x ty in {8, ..., 128}, and, for a case that steps in tiles of one
    lane per node by default, the tile shapes of its size; D3Q19: the two passes, where they
    are the default, and six column sections with their
@@ -470,8 +470,8 @@ int vclb_batch_step(vclb_batch* b, int64_t nsteps, int32_t use_graph, void* stre
    candidate on the current state (saved and restored), then the four fastest three times
    more with 2 * steps steps each, in alternation, keeping each one's best time (the leading
    shapes often lie within timing noise of each other); or take them from the JSON-lines
-   file cache_path when that holds an entry for this batch; a measured choice is appended
-   to cache_path (NULL: no file). */
+   file cache_path when that holds an entry for this batch that says whether lane tiles were
+   chosen (older ones do not); a measured choice is appended to cache_path (NULL: no file). */
 int vclb_batch_autotune(vclb_batch* b, const char* cache_path, int32_t steps, void* stream);
 
 /* Fit the cut of the batch into runs to the speed of each resident workgroup slot.  The

@@ -945,7 +945,8 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
   const vclb_params& p = c->p;
   const std::string desc = "case:" + std::to_string(p.lattice) + ":" + std::to_string(p.storage) + ":" +
                            std::to_string(p.mode) + ":" + std::to_string(p.nx) + "x" + std::to_string(p.ny) + "x" +
-                           std::to_string(p.nz) + (wall_y(p) ? "w" : "p") + std::to_string(std::max(1, p.nlabels));
+                           std::to_string(p.nz) + (wall_y(p) ? "w" : "p") + std::to_string(std::max(1, p.nlabels)) +
+                           (c->lay.J[0] != c->lay.J[1] ? "m" : "");   // m: may take several steps in a launch
   char key[32];
   std::snprintf(key, sizeof(key), "%016llx", static_cast<unsigned long long>(fnv1a(desc.data(), desc.size())));
   if (cache_path) {
@@ -958,14 +959,18 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
         const char* pb = std::strstr(line, "\"bx\": ");
         const char* pt = std::strstr(line, "\"ty\": ");
         const char* py = std::strstr(line, "\"by3\": ");
-        if (pb && pt && py) {
+        // log2 of the sides of a lane tile (0, 0: none), and whether two passes; an entry that
+        // does not say was timed before these forms were candidates and is timed again
+        const char* pl = std::strstr(line, "\"lane_tile\": [");
+        const char* pf = std::strstr(line, "\"flat\": ");
+        int l0 = 0, l1 = 0;
+        if (pb && pt && py && pl && pf && std::sscanf(pl + 14, "%d, %d", &l0, &l1) == 2) {
           bx = std::atoi(pb + 6);
           ty = std::atoi(pt + 6);
           by3 = std::atoi(py + 7);
-          // "lane_tile": log2 of the sides of a tile of one lane per node (absent: a march)
-          const char* pl = std::strstr(line, "\"lane_tile\": [");
-          if (!pl || std::sscanf(pl + 14, "%d, %d", &lx, &ly) != 2) lx = ly = 0;
-          flat = std::strstr(line, "\"flat\": 1") != nullptr;   // the two-pass 3D step
+          lx = l0;
+          ly = l1;
+          flat = std::atoi(pf + 8) == 1;
         }
       }
       std::fclose(f);
@@ -2193,11 +2198,13 @@ int vclb_batch_autotune(vclb_batch* b, const char* cache_path, int32_t steps, vo
         const char* pb = std::strstr(line, "\"bx\": ");
         const char* pt = std::strstr(line, "\"ty\": ");
         const char* pf = std::strstr(line, "\"flat_pct\": ");
-        if (pb && pt && pf) {
+        // an entry from before lane tiles were a candidate is timed again
+        const char* pl = std::strstr(line, "\"lane_tiles\": ");
+        if (pb && pt && pf && pl) {
           bx = std::atoi(pb + 6);
           ty = std::atoi(pt + 6);
           fp = std::atoi(pf + 12);
-          lane = std::strstr(line, "\"lane_tiles\": 1") ? 1 : 0;
+          lane = std::atoi(pl + 14);
         }
       }
       std::fclose(f);
