@@ -245,7 +245,8 @@ int vclb_case_set_form(vclb_case* c, int32_t form, int32_t w, int32_t h);
    lattice, storage, mode, shape, boundary and label count (entries of versions that did not
    time every form are passed over); a measured choice is appended to cache_path (NULL: no file).  D2Q9 candidates: bx in {64, 128, 256} (and 512, 1024
    with 4-byte storage) x ty in {8, ..., 128}, and, for a case that steps in tiles of one
-   lane per node by default, the tile shapes of its size; D3Q19: the two passes, where they
+   lane per node by default, the tile shapes of its size (those of three steps a launch by
+   whole launches: `steps` is then rounded up to a multiple of three); D3Q19: the two passes, where they
    are the default, and six column sections with their
    planes cut to fill 1..4 workgroups per CU, and (4-byte storage) three 768-lane
    sections at one per CU.  Synchronises the stream; VCLB_ESTATE before init. */

@@ -964,7 +964,9 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
         const char* pl = std::strstr(line, "\"lane_tile\": [");
         const char* pf = std::strstr(line, "\"flat\": ");
         int l0 = 0, l1 = 0;
-        if (pb && pt && py && pl && pf && std::sscanf(pl + 14, "%d, %d", &l0, &l1) == 2) {
+        // (without "timed": three steps in a launch were timed as single ones)
+        if (pb && pt && py && pl && pf && std::strstr(line, "\"timed\": ") &&
+            std::sscanf(pl + 14, "%d, %d", &l0, &l1) == 2) {
           bx = std::atoi(pb + 6);
           ty = std::atoi(pt + 6);
           by3 = std::atoi(py + 7);
@@ -1025,6 +1027,11 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
         if (!dup) cands.push_back(t);
       }
   }
+  // tiles of three steps a launch take only whole launches as fast as in use (one step in
+  // such a tile costs about two): with them, every candidate is timed over a multiple of three
+  bool multi = false;
+  for (const vclb::Tile& t : cands) multi = multi || vclb::tile2d_multi_ok(t.lx, t.ly);
+  const int64_t timed = multi ? (int64_t(steps) + 2) / 3 * 3 : steps;
   hipStream_t s = as_stream(stream);
   if (int rc0 = flush_pending(c, s)) return rc0;
   HIP_TRY(hipStreamSynchronize(s));
@@ -1047,12 +1054,12 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
     c->tile = t;
     if ((rc = do_steps(c, 1, stream, true))) break;
     if ((e = hipEventRecord(e0, s)) != hipSuccess) break;
-    if ((rc = do_steps(c, steps, stream, true))) break;
+    if ((rc = do_steps(c, timed, stream, true))) break;
     if ((e = hipEventRecord(e1, s)) != hipSuccess) break;
     if ((e = hipEventSynchronize(e1)) != hipSuccess) break;
     float m = 0;
     if ((e = hipEventElapsedTime(&m, e0, e1)) != hipSuccess) break;
-    ms[i] = m / float(steps);
+    ms[i] = m / float(timed);
   }
   (void)hipStreamSynchronize(s);
   (void)hipMemcpyAsync(c->ws, save, c->lay.total, hipMemcpyDeviceToDevice, s);
@@ -1074,10 +1081,12 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
   if (cache_path) {
     if (FILE* f = std::fopen(cache_path, "a")) {
       const vclb::Tile& b = c->tile;
-      std::fprintf(f, "{\"key\": \"%s\", \"shape\": \"%s\", \"bx\": %d, \"ty\": %d, \"by3\": %d, \"lane_tile\": [%d, %d], \"flat\": %d, \"ms_per_step\": %.6f, \"candidates\": [",
-                   key, desc.c_str(), b.bx, b.ty, b.by3, b.lx, b.ly, b.flat ? 1 : 0, double(ms[size_t(best)]));
+      std::fprintf(f, "{\"key\": \"%s\", \"shape\": \"%s\", \"bx\": %d, \"ty\": %d, \"by3\": %d, \"lane_tile\": [%d, %d], \"flat\": %d, \"timed\": %lld, \"ms_per_step\": %.6f, \"candidates\": [",
+                   key, desc.c_str(), b.bx, b.ty, b.by3, b.lx, b.ly, b.flat ? 1 : 0, static_cast<long long>(timed),
+                   double(ms[size_t(best)]));
       for (size_t i = 0; i < cands.size(); ++i)
-        std::fprintf(f, "%s[%d, %d, %d, %.6f]", i ? ", " : "", cands[i].bx, cands[i].ty, cands[i].by3, double(ms[i]));
+        std::fprintf(f, "%s[%d, %d, %d, %d, %d, %d, %.6f]", i ? ", " : "", cands[i].bx, cands[i].ty, cands[i].by3,
+                     cands[i].lx, cands[i].ly, cands[i].flat ? 1 : 0, double(ms[i]));
       std::fprintf(f, "]}\n");
       std::fclose(f);
     }

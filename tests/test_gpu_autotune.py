@@ -72,3 +72,24 @@ def test_a_batch_view_does_not_read_a_case_of_its_own(tmp_path):
     view.step(4)
     for x, y in zip(c.get_state(), view.get_state()):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("steps", [1, 2, 5])
+def test_three_steps_a_launch_are_timed_by_whole_launches(tmp_path, steps):
+    """Single steps in such a tile cost about two; the entry says how many steps were timed,
+    and lists every candidate with its form."""
+    from paper_2505_10899_amd import vclb as v
+    path = str(tmp_path / "tiles.jsonl")
+    p, phi0 = _case(256, 256, "fp64", mode="vortex", U0=0.04, T=400.0, mobility=0.02)
+    c = v.Case(p).init(phi0)
+    c.autotune(path, steps=steps)
+    (line,) = _lines(path)
+    e = json.loads(line)
+    lanes = [tuple(k[3:5]) for k in e["candidates"] if k[3]]
+    assert lanes == [(3, 3), (4, 4), (4, 3), (6, 2), (7, 2)]
+    assert e["timed"] % 3 == 0 and steps <= e["timed"] < steps + 3
+    p, phi0 = _case(300, 333)              # none among the candidates
+    c = v.Case(p).init(phi0)
+    c.autotune(path, steps=steps)
+    e = json.loads(_lines(path)[1])
+    assert e["timed"] == steps and [tuple(k[3:5]) for k in e["candidates"] if k[3]] == [(4, 3), (6, 2), (7, 2)]
