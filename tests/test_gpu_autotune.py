@@ -93,3 +93,42 @@ def test_three_steps_a_launch_are_timed_by_whole_launches(tmp_path, steps):
     c.autotune(path, steps=steps)
     e = json.loads(_lines(path)[1])
     assert e["timed"] == steps and [tuple(k[3:5]) for k in e["candidates"] if k[3]] == [(4, 3), (6, 2), (7, 2)]
+
+
+@pytest.mark.parametrize("nz", [1, 24])
+@pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s"])
+def test_no_candidate_changes_results(tmp_path, storage, nz):
+    """Each candidate that the tuner lists, chosen through the tune file, continues the run as
+    the default does, bit for bit."""
+    from paper_2505_10899_amd import vclb as v
+    path = str(tmp_path / "tiles.jsonl")
+    nx, ny = (130, 67) if nz == 1 else (44, 30)
+    c1 = (0.4 * nx + 0.2, 0.5 * ny + 0.3, 0.0)
+    p = W.CaseParams(lattice="D2Q9" if nz == 1 else "D3Q19", nx=nx, ny=ny, nz=nz, storage=storage, rho_light=0.1,
+                     label_centres=[c1])
+    y, x = np.mgrid[0:ny, 0:nx]
+    phi0 = np.broadcast_to(0.5 + 0.5 * np.tanh(2.0 * (0.25 * min(nx, ny) - np.hypot(x - c1[0], y - c1[1])) / p.W),
+                           (nz, ny, nx)).copy()
+    u0 = np.zeros((p.dim, nz, ny, nx))
+    u0[0] = 0.02 * np.sin(2 * np.pi * y / ny)
+    c = v.Case(p).init(phi0, u0)
+    c.autotune(path, steps=3)
+    (line,) = _lines(path)
+    entry = json.loads(line)
+    ref = v.Case(p).init(phi0, u0)
+    ref.step(7)
+    ref = ref.get_state()
+    timed = [k for k in entry["candidates"] if k[-1] > 0]
+    # 2D: lane tiles (16 x 16 not in coupled FP64) and 5 heights of 3 or 5 widths of march
+    assert len(timed) >= ((4 + 15 if storage == "fp64" else 5 + 25) if nz == 1 else (1 if storage == "fp32" else 10))
+    for bx, ty, by3, lx, ly, flat, _ in timed:
+        print("case:", storage, nz, (bx, ty, by3, lx, ly, flat), flush=True)
+        new = dict(entry, bx=bx, ty=ty, by3=by3, lane_tile=[lx, ly], flat=flat)
+        open(path, "w").write(json.dumps(new) + "\n")
+        d = v.Case(p).init(phi0, u0)
+        d.autotune(path, steps=3)
+        assert len(_lines(path)) == 1
+        assert d.form()[0] == ("lane_tiles" if lx else "two_passes" if flat else "march")
+        d.step(7)
+        for a, b in zip(d.get_state(), ref):
+            assert np.array_equal(a, b)
