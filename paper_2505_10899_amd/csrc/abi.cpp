@@ -33,6 +33,7 @@ int fail(int code, const std::string& msg) {
 }
 
 int hip_fail(hipError_t e, const char* what) {
+  (void)hipGetLastError();   // reported here, not by the next launch's check
   return fail(VCLB_EHIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
@@ -649,6 +650,7 @@ static int case_create(const vclb_params* p, void* workspace, size_t workspace_b
   } else {
     void* m = nullptr;
     hipError_t e = hipMalloc(&m, lay.total);
+    if (e != hipSuccess) (void)hipGetLastError();   // as in hip_fail
     if (e != hipSuccess) {
       delete c;
       return fail(e == hipErrorOutOfMemory ? VCLB_ENOMEM : VCLB_EHIP, "hipMalloc of the case workspace failed");
@@ -1209,6 +1211,7 @@ int vclb_reduce(vclb_case* c, const int32_t* labels, int32_t nlabels, vclb_obs* 
       c->lab_scratch = nullptr;
       c->lab_scratch_bytes = 0;
       if (hipMalloc(&c->lab_scratch, need) != hipSuccess) {
+        (void)hipGetLastError();
         c->lab_scratch = nullptr;
         return fail(VCLB_ENOMEM, "label reduction scratch");
       }
@@ -1805,6 +1808,7 @@ int vclb_batch_create(const vclb_params* cases, int32_t ncases, vclb_batch** out
   void* m = nullptr;
   hipError_t e = hipMalloc(&m, total);
   if (e != hipSuccess) {
+    (void)hipGetLastError();
     delete b;
     return fail(e == hipErrorOutOfMemory ? VCLB_ENOMEM : VCLB_EHIP, "hipMalloc of the batch workspace failed");
   }
@@ -2503,8 +2507,10 @@ int vclb_adjoint_record(vclb_case* c, const double* phi0, const double* u0, int 
   if (m && c->adj_mem_bytes < lay.total) return fail(VCLB_ENOMEM, "the adjoint store given is too small");
   if (lay.own) {
     const hipError_t e = hipMalloc(&m, lay.total);
-    if (e != hipSuccess)
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
       return fail(e == hipErrorOutOfMemory ? VCLB_ENOMEM : VCLB_EHIP, "hipMalloc of the adjoint store failed");
+    }
   }
   c->adj = new (std::nothrow) AdjStore(lay);
   if (!c->adj) {

@@ -170,6 +170,17 @@ def check(rc: int):
         raise VclbError(rc, f"{L.vclb_strerror(rc).decode()}: {L.vclb_last_error().decode()}")
 
 
+def _with_memory(call) -> int:
+    """Status of a library call that allocates device memory of its own.  torch's allocator
+    keeps what cases have given back (workspaces, adjoint stores) and the library cannot use
+    it: a call that finds no memory is made again once the cache is empty."""
+    rc = call()
+    if rc == VCLB_ENOMEM or (rc == VCLB_EHIP and b"out of memory" in lib().vclb_last_error()):
+        torch.cuda.empty_cache()
+        rc = call()
+    return rc
+
+
 def to_cparams(p) -> Params:
     """CaseParams (workloads.CaseParams or any object with the same fields) -> C struct."""
     c = Params()
@@ -280,7 +291,7 @@ class Case:
         """Time the candidate tiles on the current state (restored afterwards) and keep the
         fastest; returns (bx, ty, by3), the march's shape: form() says what was chosen."""
         path = cache_path.encode() if cache_path else None
-        check(lib().vclb_case_autotune(self.h, path, int(steps), _stream_handle(stream)))
+        check(_with_memory(lambda: lib().vclb_case_autotune(self.h, path, int(steps), _stream_handle(stream))))
         return self.tile()
 
     def set_reduce_every(self, every: int):
@@ -453,7 +464,7 @@ class Case:
         nl = int(nlabels) if nlabels else int(lab.max().item()) + 1
         arr = (Obs * max(1, nl))()
         fn = lib().vclb_reduce_static if static else lib().vclb_reduce
-        rc = fn(self.h, ctypes.c_void_p(lab.data_ptr()), nl, arr, _stream_handle(stream))
+        rc = _with_memory(lambda: fn(self.h, ctypes.c_void_p(lab.data_ptr()), nl, arr, _stream_handle(stream)))
         if rc not in (VCLB_OK, VCLB_ENONFINITE):
             check(rc)
         out = _obs_to_dict(arr, max(1, nl))
@@ -599,7 +610,7 @@ class Batch:
         n = len(params_list)
         arr = (Params * n)(*[to_cparams(p) for p in params_list])
         h = ctypes.c_void_p()
-        check(lib().vclb_batch_create(arr, n, ctypes.byref(h)))
+        check(_with_memory(lambda: lib().vclb_batch_create(arr, n, ctypes.byref(h))))
         self.h = h
         self.device = torch.device(device)
         self.params = list(params_list)
@@ -693,7 +704,7 @@ class Batch:
 
     def autotune(self, cache_path=None, steps: int = 5, stream=None):
         path = cache_path.encode() if cache_path else None
-        check(lib().vclb_batch_autotune(self.h, path, int(steps), _stream_handle(stream)))
+        check(_with_memory(lambda: lib().vclb_batch_autotune(self.h, path, int(steps), _stream_handle(stream))))
         return self.tile()
 
     def weights(self) -> np.ndarray:
@@ -715,5 +726,6 @@ class Batch:
         """Re-cut the runs to the measured speed of each workgroup slot (state restored);
         returns the slowest slot's time before over after."""
         g = ctypes.c_double(1.0)
-        check(lib().vclb_batch_balance(self.h, int(rounds), int(steps), ctypes.byref(g), _stream_handle(stream)))
+        check(_with_memory(lambda: lib().vclb_batch_balance(self.h, int(rounds), int(steps), ctypes.byref(g),
+                                                            _stream_handle(stream))))
         return g.value

@@ -40,3 +40,49 @@ def test_adjoint_store_came_with_a_new_minor_version():
     v = _vclb()
     assert "vclb_adjoint_set_store" in v.exported_symbols()
     assert v.lib().vclb_version() == v.VERSION >= 20200
+
+
+class _Library:
+    """Every entry point succeeds, but for those given."""
+
+    def __init__(self, **special):
+        self.special = special
+        self.calls = []
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.calls.append(name)
+            f = self.special.get(name)
+            return f(*args) if f else 0
+        return call
+
+
+@pytest.mark.parametrize("first", ["none", "memory", "hip"])
+def test_memory_in_torchs_cache_is_given_back_to_the_library(monkeypatch, first):
+    """A case's adjoint store (or workspace) stays in torch's cache after the case: a library
+    call that then finds no memory is made again with the cache emptied."""
+    import workloads as W
+    v = _vclb()
+    given_back = []
+    status = {"none": [0], "memory": [v.VCLB_ENOMEM, 0], "hip": [v.VCLB_EHIP, 0]}[first]
+    answers = iter(status)
+    fake = _Library(vclb_batch_create=lambda *a: next(answers),
+                    vclb_last_error=lambda: b"hipMalloc(&save, bytes): out of memory")
+    monkeypatch.setattr(v, "lib", lambda: fake)
+    monkeypatch.setattr(v.torch.cuda, "empty_cache", lambda: given_back.append(1))
+    p, _, _ = W.two_droplets()
+    v.Batch([p])
+    assert fake.calls.count("vclb_batch_create") == len(status) and len(given_back) == len(status) - 1
+
+
+def test_other_errors_are_not_tried_again(monkeypatch):
+    import workloads as W
+    v = _vclb()
+    fake = _Library(vclb_batch_create=lambda *a: v.VCLB_EHIP, vclb_last_error=lambda: b"batch set-up: unknown error",
+                    vclb_strerror=lambda rc: b"HIP error")
+    monkeypatch.setattr(v, "lib", lambda: fake)
+    monkeypatch.setattr(v.torch.cuda, "empty_cache", lambda: pytest.fail("not a lack of memory"))
+    p, _, _ = W.two_droplets()
+    with pytest.raises(v.VclbError):
+        v.Batch([p])
+    assert fake.calls.count("vclb_batch_create") == 1
