@@ -650,8 +650,8 @@ static int case_create(const vclb_params* p, void* workspace, size_t workspace_b
   } else {
     void* m = nullptr;
     hipError_t e = hipMalloc(&m, lay.total);
-    if (e != hipSuccess) (void)hipGetLastError();   // as in hip_fail
     if (e != hipSuccess) {
+      (void)hipGetLastError();
       delete c;
       return fail(e == hipErrorOutOfMemory ? VCLB_ENOMEM : VCLB_EHIP, "hipMalloc of the case workspace failed");
     }

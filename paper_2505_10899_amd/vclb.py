@@ -229,6 +229,23 @@ def _stream_handle(stream=None):
     return ctypes.c_void_p(s.cuda_stream)
 
 
+def _as_torch_stream(stream, device):
+    if stream is None:
+        return torch.cuda.current_stream()
+    return stream if isinstance(stream, torch.cuda.Stream) else torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+
+
+def _stream_with_tensors(stream, device):
+    """The stream of a call that is handed tensors of this binding's own.  They are made on
+    torch's current stream, in memory whose last use there may still be running: another
+    stream first waits for it.  Until the caller has synchronised the stream returned they
+    have to be kept."""
+    s = _as_torch_stream(stream, device)
+    if stream is not None:
+        s.wait_stream(torch.cuda.current_stream())
+    return s
+
+
 class Case:
     """One simulation case living on the GPU.
 
@@ -305,10 +322,10 @@ class Case:
             u = torch.as_tensor(np.ascontiguousarray(u0, dtype=np.float64).reshape(-1)).to(self.device)
         if not torch.isfinite(phi).all():
             raise VclbError(VCLB_ENONFINITE, "phi0 has a NaN/Inf")
+        s = _stream_with_tensors(stream, self.device)
         check(lib().vclb_case_init(self.h, ctypes.c_void_p(phi.data_ptr()),
-                                   ctypes.c_void_p(u.data_ptr() if u is not None else 0), DEVICE,
-                                   _stream_handle(stream)))
-        torch.cuda.current_stream().synchronize()
+                                   ctypes.c_void_p(u.data_ptr() if u is not None else 0), DEVICE, _stream_handle(s)))
+        s.synchronize()
         return self
 
     def set_state(self, g, f, J, t: int, stream=None):
@@ -316,9 +333,10 @@ class Case:
         dev = lambda a: torch.as_tensor(np.ascontiguousarray(a, dtype=np.float64).reshape(-1)).to(self.device)
         tg, tJ = dev(g), dev(J)
         tf = dev(f) if self.p.mode == "coupled" else None
+        s = _stream_with_tensors(stream, self.device)   # the library synchronises it
         check(lib().vclb_case_set_state(self.h, ctypes.c_void_p(tg.data_ptr()),
                                         ctypes.c_void_p(tf.data_ptr() if tf is not None else 0),
-                                        ctypes.c_void_p(tJ.data_ptr()), int(t), DEVICE, _stream_handle(stream)))
+                                        ctypes.c_void_p(tJ.data_ptr()), int(t), DEVICE, _stream_handle(s)))
         return self
 
     def state_device(self, stream=None):
@@ -328,10 +346,10 @@ class Case:
         g = torch.empty(Q * self.n, dtype=torch.float64, device=self.device)
         J = torch.empty(self.D * self.n, dtype=torch.float64, device=self.device)
         f = torch.empty(Q * self.n, dtype=torch.float64, device=self.device) if self.p.mode == "coupled" else None
+        s = _stream_with_tensors(stream, self.device)   # the library synchronises it
         check(lib().vclb_case_get_state(self.h, ctypes.c_void_p(g.data_ptr()),
                                         ctypes.c_void_p(f.data_ptr() if f is not None else 0),
-                                        ctypes.c_void_p(J.data_ptr()), DEVICE, _stream_handle(stream)))
-        torch.cuda.current_stream().synchronize()
+                                        ctypes.c_void_p(J.data_ptr()), DEVICE, _stream_handle(s)))
         return g, f, J
 
     def get_state(self, stream=None):
@@ -341,10 +359,10 @@ class Case:
         g = torch.empty(Q * self.n, dtype=torch.float64, device=self.device)
         J = torch.empty(self.D * self.n, dtype=torch.float64, device=self.device)
         f = torch.empty(Q * self.n, dtype=torch.float64, device=self.device) if self.p.mode == "coupled" else None
+        s = _stream_with_tensors(stream, self.device)   # the library synchronises it
         check(lib().vclb_case_get_state(self.h, ctypes.c_void_p(g.data_ptr()),
                                         ctypes.c_void_p(f.data_ptr() if f is not None else 0),
-                                        ctypes.c_void_p(J.data_ptr()), DEVICE, _stream_handle(stream)))
-        torch.cuda.current_stream().synchronize()
+                                        ctypes.c_void_p(J.data_ptr()), DEVICE, _stream_handle(s)))
         g = g.cpu().numpy().reshape((Q,) + shape)
         J = J.cpu().numpy().reshape((self.D,) + shape)
         f = f.cpu().numpy().reshape((Q,) + shape) if f is not None else None
@@ -371,8 +389,8 @@ class Case:
                  (FIELD_MU, "mu", 1), (FIELD_PSI, "psi", 1)]
         total = sum(k for b, _, k in sizes if mask & b) * self.n
         out = torch.empty(total, dtype=torch.float64, device=self.device)
-        check(lib().vclb_observe(self.h, mask, ctypes.c_void_p(out.data_ptr()), DEVICE, _stream_handle(stream)))
-        torch.cuda.current_stream().synchronize()
+        s = _stream_with_tensors(stream, self.device)   # the library synchronises it
+        check(lib().vclb_observe(self.h, mask, ctypes.c_void_p(out.data_ptr()), DEVICE, _stream_handle(s)))
         a = out.cpu().numpy()
         shape = (self.p.nz, self.p.ny, self.p.nx)
         res, off = {}, 0
@@ -404,9 +422,10 @@ class Case:
         if not torch.isfinite(phi).all():
             raise VclbError(VCLB_ENONFINITE, "phi0 has a NaN/Inf")
         self._adjoint_store(nsteps, every, stream)
+        s = _stream_with_tensors(stream, self.device)   # the library synchronises it
         check(lib().vclb_adjoint_record(self.h, ctypes.c_void_p(phi.data_ptr()),
                                         ctypes.c_void_p(u.data_ptr() if u is not None else 0), DEVICE,
-                                        int(nsteps), int(every), _stream_handle(stream)))
+                                        int(nsteps), int(every), _stream_handle(s)))
         return self
 
     def _adjoint_store(self, nsteps: int, every: int, stream):
@@ -414,10 +433,7 @@ class Case:
         rollouts of an optimisation (hipMalloc and hipFree of 0.5 GB cost 0.6 ms of a 3.4 ms
         rollout).  Allocated on the stream that uses it; every record and run ends with its
         stream synchronised, so it is free of work when it is given back."""
-        where = contextlib.nullcontext()
-        if stream is not None:
-            where = torch.cuda.stream(stream if isinstance(stream, torch.cuda.Stream) else
-                                      torch.cuda.ExternalStream(stream.cuda_stream, device=self.device))
+        where = torch.cuda.stream(_as_torch_stream(stream, self.device)) if stream is not None else contextlib.nullcontext()
         n = ctypes.c_size_t()
         check(lib().vclb_adjoint_bytes(ctypes.byref(self.cp), int(nsteps), int(every), ctypes.byref(n)))
         check(lib().vclb_adjoint_set_store(self.h, None, 0))
@@ -440,8 +456,9 @@ class Case:
             raise VclbError(VCLB_EINVAL, "seed must hold 10 weights per label")
         dphi = torch.empty(self.n, dtype=torch.float64, device=self.device)
         out = (ctypes.c_double * 2)()
+        s = _stream_with_tensors(stream, self.device)   # the library synchronises it
         check(lib().vclb_adjoint_run(self.h, sd.ctypes.data_as(_P(ctypes.c_double)), float(normal_tau),
-                                     ctypes.c_void_p(dphi.data_ptr()), DEVICE, out, _stream_handle(stream)))
+                                     ctypes.c_void_p(dphi.data_ptr()), DEVICE, out, _stream_handle(s)))
         return dphi.reshape(self.p.nz, self.p.ny, self.p.nx), out[0], out[1]
 
     def reduce(self, stream=None) -> dict:
@@ -464,7 +481,8 @@ class Case:
         nl = int(nlabels) if nlabels else int(lab.max().item()) + 1
         arr = (Obs * max(1, nl))()
         fn = lib().vclb_reduce_static if static else lib().vclb_reduce
-        rc = _with_memory(lambda: fn(self.h, ctypes.c_void_p(lab.data_ptr()), nl, arr, _stream_handle(stream)))
+        s = _stream_with_tensors(stream, self.device)   # the library synchronises it
+        rc = _with_memory(lambda: fn(self.h, ctypes.c_void_p(lab.data_ptr()), nl, arr, _stream_handle(s)))
         if rc not in (VCLB_OK, VCLB_ENONFINITE):
             check(rc)
         out = _obs_to_dict(arr, max(1, nl))
@@ -646,8 +664,9 @@ class Batch:
         n = len(phis)
         pp = (ctypes.c_void_p * n)(*[t.data_ptr() for t in phis])
         up = (ctypes.c_void_p * n)(*[t.data_ptr() if t is not None else 0 for t in us])
-        check(lib().vclb_batch_init(self.h, pp, up, DEVICE, _stream_handle(stream)))
-        torch.cuda.current_stream().synchronize()
+        s = _stream_with_tensors(stream, self.device)
+        check(lib().vclb_batch_init(self.h, pp, up, DEVICE, _stream_handle(s)))
+        s.synchronize()
         return self
 
     def nodes(self) -> int:

@@ -86,3 +86,40 @@ def test_other_errors_are_not_tried_again(monkeypatch):
     with pytest.raises(v.VclbError):
         v.Batch([p])
     assert fake.calls.count("vclb_batch_create") == 1
+
+
+class _Stream:
+    def __init__(self, log, name, handle):
+        self.log, self.name, self.cuda_stream = log, name, handle
+
+    def synchronize(self):
+        self.log.append(f"synchronize {self.name}")
+
+    def wait_stream(self, other):
+        self.log.append(f"{self.name} after {other.name}")
+
+
+@pytest.mark.parametrize("call", ["init", "batch"])
+def test_tensors_of_a_call_on_another_stream_live_until_it_is_done(monkeypatch, call):
+    """init uploads its fields on torch's current stream and drops them at its end: the stream
+    it was given has to come after their making, and has to be waited for."""
+    import workloads as W
+    v = _vclb()
+    log = []
+    cur, side = _Stream(log, "current", 1), _Stream(log, "side", 2)
+    fake = _Library(vclb_case_init=lambda *a: log.append(f"launch on {a[-1].value}") or 0,
+                    vclb_batch_init=lambda *a: log.append(f"launch on {a[-1].value}") or 0)
+    monkeypatch.setattr(v, "lib", lambda: fake)
+    monkeypatch.setattr(v.torch.cuda, "Stream", _Stream)
+    monkeypatch.setattr(v.torch.cuda, "current_stream", lambda *a: cur)
+    p, phi0, u0 = W.two_droplets()
+    if call == "init":
+        c = v.Case(p, device="cpu", _borrowed=(object(), ctypes.c_void_p()))
+        c.init(phi0, u0, stream=side)
+    else:
+        v.Batch([p], device="cpu").init([(phi0, u0)], stream=side)
+    assert log == ["side after current", "launch on 2", "synchronize side"]
+    log.clear()
+    if call == "init":
+        c.init(phi0, u0)
+        assert log == ["launch on 1", "synchronize current"]
