@@ -87,31 +87,31 @@ __device__ __forceinline__ void tile2d_sums(const Case& c, const PhiPsi* ring, i
   }
 }
 
-// f of a node just updated, on its way to the stored type.  In 2 bytes a value is rounded
-// either to 4 bytes first or once, together with the multiply-add that forms it.  Which of
-// the two is that of the march the case would otherwise run, so that its results are the
-// march's bit for bit: the compiled march of a single case rounds the directions that take
-// no wall term once (ONCE), a batch's strips none and its bands direction 0 (`band`).
-// e holds these directions encoded.
+// f of a node just updated, on its way to a 2-byte storage: a value is rounded either to 4
+// bytes first or once, together with the multiply-add that forms it.  Which of the two is
+// that of the march the case would otherwise run, so that its results are the march's bit
+// for bit: the compiled march of a single case rounds the directions that take no wall term
+// once, a batch's strips none and its bands direction 0 (`band`).  These directions are
+// encoded first, before the wall terms.
 enum class Once { Level, OfBand };
-template <Once ONCE>
-constexpr bool encoded_first(int i) { return D2Q9::cy[i] == 0 && (ONCE == Once::Level || i == 0); }
+template <class St, Once ONCE>
+constexpr bool encoded_first(int i) {
+  return sizeof(typename St::S) == 2 && D2Q9::cy[i] == 0 && (ONCE == Once::Level || i == 0);
+}
 template <class St, Once ONCE>
 __device__ __forceinline__ void encode_first(const typename St::R (&f)[9], bool band, typename St::S (&e)[4]) {
+  if constexpr (sizeof(typename St::S) == 2) {
 #pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    if (!encoded_first<ONCE>(i)) continue;
-    typename St::S a = St::enc(f[i]);
-    if constexpr (sizeof(typename St::S) == 2) {
-      unsigned u = __half_as_ushort(a);
+    for (int i = 0; i < 9; ++i) {
+      if (!encoded_first<St, ONCE>(i)) continue;
+      unsigned u = __half_as_ushort(St::enc(f[i]));
       asm("" : "+v"(u));   // on its own: not converted after the choice below
-      a = __ushort_as_half((unsigned short)u);
+      e[i & 3] = __ushort_as_half((unsigned short)u);
       if (ONCE != Once::Level) {
         const typename St::S b = St::enc(rounded(f[i]));   // both, with no branch (which would part the update)
-        a = band ? a : b;
+        e[i & 3] = band ? e[i & 3] : b;
       }
     }
-    e[i & 3] = a;
   }
 }
 
@@ -232,7 +232,7 @@ __device__ __forceinline__ void tile2d_step(const DevCase<D2Q9, St>& c, long t, 
       encode_first<St, ONCE>(f, band, e);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (encoded_first<ONCE>(i)) store_f(i, e[i]);
+        if (encoded_first<St, ONCE>(i)) store_f(i, e[i]);
     }
     R res = R(0);   // rounding of the stored g deviations, taken off the stored phi
 #pragma unroll
@@ -258,7 +258,7 @@ __device__ __forceinline__ void tile2d_step(const DevCase<D2Q9, St>& c, long t, 
       }
 #pragma unroll
       for (int i = 0; i < Q; ++i)
-        if (!encoded_first<ONCE>(i)) store_f(i, St::enc(f[i]));
+        if (!encoded_first<St, ONCE>(i)) store_f(i, St::enc(f[i]));
     }
     stg(c.Jw, nn, J[0]);
     stg(c.Jw + ns, nn, J[1]);
@@ -417,7 +417,7 @@ __device__ __forceinline__ void tile2d_multi(const DevCase<D2Q9, St>& c, long t,
             if (L::cy[i] > 0) f[i] += c.np.wt[i] * out.rho;
         }
       }
-      auto stored_f = [&](int i) -> S { return encoded_first<Once::Level>(i) ? e[i & 3] : St::enc(f[i]); };
+      auto stored_f = [&](int i) -> S { return encoded_first<St, Once::Level>(i) ? e[i & 3] : St::enc(f[i]); };
       const float own_phi = St::shifted ? float(in.nphi[0] - res) : 0.0f;
       if (m > 0) {
 #pragma unroll
