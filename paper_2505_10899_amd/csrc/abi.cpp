@@ -457,16 +457,47 @@ bool two_passes_ok(const vclb_params& p) {
   return p.lattice == VCLB_D3Q19 && long(p.nx) * p.ny * p.nz <= (1L << 28) - 1;
 }
 
+// whether every rate outside the g flux and f stress rows is 1
+bool unit_rates(const vclb_params& p) {
+  double sg[19], sf[19];
+  fill_rates(p, sg, sf);
+  for (int k = 0; k < lattice_q(p.lattice); ++k) {
+    const bool flux = p.lattice == VCLB_D2Q9 ? vclb::D2Q9::g_flux_row[k] : vclb::D3Q19::g_flux_row[k];
+    const bool stress = p.lattice == VCLB_D2Q9 ? vclb::D2Q9::f_stress_row[k] : vclb::D3Q19::f_stress_row[k];
+    if ((!flux && sg[k] != 1.0) || (!stress && sf[k] != 1.0)) return false;
+  }
+  return true;
+}
+
 // Whether a 3D case steps in two passes in stored order (flat3d.hip) or as a section march.
-// The march wins where its sections and rows fit: from 2^21 nodes on, rows that start on
-// cache lines, 4- or 8-byte storage (96 x 96 x 384 FP32 263 / 296 us a step, FP64 505 / 566;
-// 64 x 64 x 300 FP32 115 / 102).  FP16S moves few enough bytes that the second reading of g
-// costs little (96 x 96 x 384 200 / 202, 128 x 128 x 200 240 / 184).
+// The march reads g once, but only sections that fit the grid without idle lanes, with rows
+// that start on cache lines and long marches, make up for its round trips.  Measured on 32
+// grids of 0.3 to 7 million nodes, periodic and with walls, with unequal viscosities and
+// general rates (us a step, march / two passes):
+//  - FP64: rows on lines from 2^21 nodes on (96 x 96 x 384 506 / 555), and from 2^20 where
+//    sections of 32 columns fill the rows (64 x 64 x 350 210 / 224, 96 x 96 x 200 271 / 298,
+//    256 x 64 x 64 163 / 172; 96 x 96 x 100 149 / 152; but 80 x 80 x 300 298 / 303);
+//  - FP32: rows on lines from 2^21 nodes on (96 x 96 x 384 263 / 291), and from 1.3 million
+//    where sections of 96 columns fill the rows (96 x 96 x 150 117 / 126, 96 x 8 x 2000
+//    125 / 131; 192 x 32 x 200, 1.2 million, 114 / 107), but not with general rates (96 x 96 x
+//    200 189 / 161);
+//  - FP16S, whose second reading of g is cheap: periodic from 1.3 million nodes on, where one
+//    section spans the rows and is its own halo (96 x 96 x 200 110 / 121, 96 x 8 x 2000 76 / 91,
+//    32 x 64 x 1000 119 / 126) or the grid has only 8 or 16 rows (64 x 16 x 1500 78 / 89), else
+//    two passes (64 x 64 x 350 76 / 75, 128 x 128 x 400 351 / 356, 256 x 256 x 100 457 / 356;
+//    with walls 96 x 96 x 384 221 / 195).
 bool flat3d_chosen(const vclb_params& p) {
   const long n = long(p.nx) * p.ny * p.nz;
   if (!two_passes_ok(p)) return false;
-  const bool lines = size_t(p.nx) * storage_bytes(p.storage) % 128 == 0;
-  return !(p.storage != VCLB_FP16S && lines && n >= (1L << 21));
+  constexpr long kMiddle = 5L << 18;
+  if (p.storage == VCLB_FP16S) {
+    const bool spans = (p.nx == 96 || p.nx == 32) && p.ny % 8 == 0;
+    const bool few_rows = p.nx % 32 == 0 && p.nx < 96 && (p.ny == 8 || p.ny == 16);
+    return wall_y(p) || n < kMiddle || !(spans || few_rows);
+  }
+  if (size_t(p.nx) * storage_bytes(p.storage) % 128 != 0) return true;
+  if (p.storage == VCLB_FP64) return !(n >= (1L << 21) || (n >= (1L << 20) && p.nx % 32 == 0));
+  return !(n >= (1L << 21) || (n >= kMiddle && p.nx % 96 == 0 && unit_rates(p)));
 }
 
 vclb::Tile default_tile(const vclb_params& p, int ncu, bool wide_ok = true, bool multi = true) {
