@@ -432,7 +432,7 @@ bool lane_tile_ok(const vclb_case& c, const vclb::Tile& t) {
 //    352 / 361; 2944 x 2944 FP32 289 / 302), except FP32 rows that do not start on cache
 //    lines (4091 x 4096 FP32 650 / 637);
 //  - beyond 2^26 nodes the tiles' 32-bit byte offsets end (three planes of 8 bytes).
-void tile2d_choose(const vclb_params& p, vclb::Tile& t, bool multi) {
+void tile2d_choose(const vclb_params& p, int ncu, vclb::Tile& t, bool multi) {
   t.lx = t.ly = 0;
   const long n = long(p.nx) * p.ny;
   const size_t sb = storage_bytes(p.storage);
@@ -442,7 +442,7 @@ void tile2d_choose(const vclb_params& p, vclb::Tile& t, bool multi) {
   if (p.storage != VCLB_FP64 && n >= (1L << 23) && !(p.storage == VCLB_FP32 && coupled && !lines)) return;
   const size_t sets = size_t(n) * 9 * sb * (coupled ? 4 : 2);
   vclb::Tile u = t;
-  auto one_per_cu = [&](int side) { return long((p.nx + side - 1) / side) * ((p.ny + side - 1) / side) <= 256; };
+  auto one_per_cu = [&](int side) { return long((p.nx + side - 1) / side) * ((p.ny + side - 1) / side) <= ncu; };
   if (multi && multi_case(p) && one_per_cu(8)) u.lx = u.ly = 3;
   else if (multi && tile2d_fits(p, vclb::Tile{t.bx, t.ty, t.by3, 4, 4}) && one_per_cu(16)) u.lx = u.ly = 4;
   else if (n <= (1L << 19)) u.lx = 4, u.ly = 3;
@@ -521,7 +521,7 @@ vclb::Tile default_tile(const vclb_params& p, int ncu, bool wide_ok = true, bool
     const long ty = (long(p.ny) + segs - 1) / segs;
     t.ty = int(std::max(8L, std::min(64L, ty)));
     t.by3 = 1;
-    tile2d_choose(p, t, multi);
+    tile2d_choose(p, ncu, t, multi);
   } else {
     // 32 x 8 columns per workgroup (a halo ring of a third of the tile, one wave per two
     // rows of 32): the fastest section measured on a 96 x 96 x 384 case.  Each workgroup
