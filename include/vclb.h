@@ -432,9 +432,9 @@ int vclb_batch_nodes(const vclb_batch* b, int64_t* nodes);
    consecutive items with about equal work, or work in proportion to the slot weights
    vclb_batch_balance measured (an item is split between rows where a run ends);
    get_tile also returns that workgroup count.  Default: bx 512, ty 1024; a batch whose
-   population sets fit the last-level cache together (256 MB) first steps in tiles of one
-   lane per node instead, until set_tile or set_schedule chooses a run shape (or autotune
-   finds one faster). */
+   state keeps well within the last-level cache (224 MB of its 256 in FP64, 200 MB in FP32
+   and FP16S) first steps in tiles of one lane per node instead, until set_tile or
+   set_schedule chooses a run shape (or autotune finds one faster). */
 int vclb_batch_set_tile(vclb_batch* b, int32_t bx, int32_t ty);
 int vclb_batch_get_tile(const vclb_batch* b, int32_t* bx, int32_t* ty, int32_t* blocks);
 

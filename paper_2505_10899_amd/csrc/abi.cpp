@@ -1707,16 +1707,25 @@ vclb::BatchArgs batch_args(const vclb_batch* b, int64_t t, int reduce) {
 }
 
 // Whether a batch steps in lane tiles (tile2d.hip), one workgroup per tile of every case,
-// and its tables; b->lx stays 0 if not.  They pay while every case's population sets fit
-// the 256 MB last-level cache together, where the runs leave CUs idle or wait for their
-// row round trips (us a step, runs / tiles: 4 cases of 35 k nodes in FP32 7.6 / 5.4, 24 of
-// 214 k in FP64 18.6 / 14.8, 68 of 1.36 M in FP32 53 / 42); beyond it the runs' single read
-// of each population wins (100 cases of 1.87 M nodes in FP32 70 / 99, 256 of 11.7 M in FP64
-// 778 / 1076).  Tiles of 64 x 4 were within 5% of 16 x 8 on every such batch.
+// and its tables; b->lx stays 0 if not.  They pay while all that a step moves (two sets of g
+// and f, J, and the two phi of 4- and 2-byte storage) stays in the 256 MB last-level cache,
+// where the runs leave CUs idle or wait for their row round trips (us a step, runs / tiles:
+// 4 cases of 35 k nodes in FP32 7.6 / 5.4, 24 of 214 k in FP64 18.6 / 14.8, 68 of 1.36 M in
+// FP32 53 / 42).  Beyond it the runs' single read of each population wins (256 of 11.7 M in
+// FP64 778 / 1076), and some way before it already, as the tiles' second read of g misses
+// with the first lines that the cache drops:
+//  - FP64 from 224 MB on (cases of 90^2: 220 MB 53.9 / 52.3, 230 MB 60.5 / 62.0; of 260^2:
+//    220 MB 46.3 / 43.7, 240 MB 60.9 / 68.1);
+//  - FP32 and FP16S from 200 MB on (FP32, 90^2: 190 MB 49.6 / 45.9, 210 MB 53.4 / 58.6,
+//    250 MB 63.2 / 82.1; 260^2: 220 MB 55.8 / 46.6, 230 MB 57.4 / 70.6; FP16S, 90^2: 200 MB
+//    63.2 / 62.5, 220 MB 68.1 / 70.0; 260^2: 200 MB 60.3 / 59.3, 230 MB 67.6 / 73.3).
+// Tiles of 64 x 4 were within 5% of 16 x 8 on every such batch.
 void batch_lane_tiles(vclb_batch* b, const vclb_params* cases, size_t items_cap, std::vector<int2>& tiles,
                       std::vector<int2>& per_case) {
   const int lx = 4, ly = 3;
-  if (size_t(b->nodes) * 9 * storage_bytes(b->storage) * 4 > (size_t(256) << 20)) return;
+  const bool fp64 = b->storage == VCLB_FP64;
+  const size_t node = 36 * storage_bytes(b->storage) + 2 * arith_bytes(b->storage) + (fp64 ? 0 : 8);
+  if (size_t(b->nodes) * node > (size_t(fp64 ? 224 : 200) << 20)) return;
   for (int k = 0; k < b->n; ++k) {
     const int nt = ((cases[k].nx + (1 << lx) - 1) >> lx) * ((cases[k].ny + (1 << ly) - 1) >> ly);
     per_case.push_back(int2{int(tiles.size()), nt});

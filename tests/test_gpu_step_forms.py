@@ -111,6 +111,27 @@ def test_batch_lane_tiles_equal_the_runs(storage):
         _same(x, y)
 
 
+@pytest.mark.parametrize("storage,side,inside,beyond", [("fp64", 262, 10, 12), ("fp32", 262, 17, 20),
+                                                        ("fp16s", 262, 31, 38)])
+def test_batch_leaves_lane_tiles_before_the_cache_is_full(storage, side, inside, beyond):
+    """Lane tiles lose to the runs where the state fills the last-level cache; the recorded sums
+    tell the two apart, as each adds in the order of its own workgroups."""
+    from paper_2505_10899_amd import vclb as v
+    for n, runs in ((inside, False), (beyond, True)):
+        print("case:", storage, n, flush=True)
+        p, phi0, u0 = _case(side, side, storage, False)
+        got = []
+        for chosen in (False, True):
+            b = v.Batch([p] * n)
+            b.init([(phi0, u0)] * n)
+            if chosen:
+                b.set_tile(*b.tile()[:2])   # the default run shape
+            b.step(3)
+            h = [c.history(0, 3) for c in b.cases]
+            got.append([[x[k].ravel() for x in h] for k in ("sum_phi", "sum_phi_d", "sum_phi_dd")])
+        assert all(np.array_equal(x, y) for x, y in zip(*got)) == runs
+
+
 LANE_SHAPES = [(8, 8), (16, 16), (16, 8), (64, 4), (128, 4)]
 
 
