@@ -504,7 +504,8 @@ int vclb_batch_get_weights(const vclb_batch* b, double* weights, int32_t capacit
 /* Set the slot weights (count = the slot count of the current launch shape, each in
    [1e-3, 1e3], rescaled to mean 1; count 0 clears them) and re-cut the runs.  They stay
    in force on the same terms as balanced ones.  Results of a step do not depend on the
-   weights. */
+   weights.  A batch in tiles of one lane per node has no runs: it keeps the weights for
+   the runs it would be cut into, and steps as before. */
 int vclb_batch_set_weights(vclb_batch* b, const double* weights, int32_t count);
 
 #ifdef __cplusplus

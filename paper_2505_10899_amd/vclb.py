@@ -735,7 +735,8 @@ class Batch:
         return np.array(buf[:n.value])
 
     def set_weights(self, w):
-        """Apply slot weights (one per slot of the current launch shape; empty clears)."""
+        """Apply slot weights (one per slot of the current launch shape; empty clears).  A
+        batch that steps in lane tiles has no runs, so they change nothing there."""
         a = np.ascontiguousarray(w, dtype=np.float64)
         check(lib().vclb_batch_set_weights(self.h, a.ctypes.data_as(ctypes.POINTER(ctypes.c_double)) if a.size else None,
                                            int(a.size)))
