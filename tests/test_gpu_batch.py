@@ -1,7 +1,7 @@
 """GPU tests of the batched path: uneven cases advanced together must reproduce each
 case advanced alone with the same tile (the single-case path is itself checked against
-the oracle), the hipGraph replay must equal eager launches, and the autotuner and the
-slot balancing must leave the state untouched."""
+the oracle), steps must not depend on how they are divided into calls, and the autotuner
+and the slot balancing must leave the state untouched."""
 import os
 import sys
 
@@ -136,6 +136,27 @@ def test_batch_graph_equals_eager_and_history():
         assert np.all(h["step"][:, 0] == np.arange(13))
         r = c.reduce()
         assert abs(r["sum_phi"][0] - h["sum_phi"][-1, 0]) <= 1e-5 * abs(r["sum_phi"][0])
+
+
+@pytest.mark.parametrize("chosen", [False, True])   # lane tiles, runs
+@pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s"])
+def test_batch_steps_do_not_depend_on_their_calls(storage, chosen):
+    """13 steps in one call equal 7 + 1 + 5, states and recorded sums, bit for bit."""
+    v = _v()
+    cases = small_batch(storage, n=5, seed=3)
+    got = []
+    for calls in ((13,), (7, 1, 5)):
+        b = v.Batch([p for p, _, _ in cases]).init([(phi0, u0) for _, phi0, u0 in cases])
+        if chosen:
+            b.set_tile(*b.tile()[:2])
+        for n in calls:
+            b.step(n)
+        got.append(([c.get_state() for c in b.cases], b.history(0, 13)))
+    for k in range(len(cases)):
+        for x, y in zip(got[0][0][k], got[1][0][k]):
+            assert np.array_equal(x, y), k
+    for f in ("step", "sum_phi", "count_half", "sum_phi_d", "sum_phi_dd"):
+        assert np.array_equal(got[0][1][f], got[1][1][f]), f
 
 
 def test_batch_reduce_and_history_match_each_case():
