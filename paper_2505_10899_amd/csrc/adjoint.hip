@@ -18,9 +18,10 @@
 //     phi itself).  Accumulates dJ/dsigma and dJ/dM per workgroup.
 // As three kernels (phi and psi, the local reverse, the stencils) a step of 512 x 256 took
 // 29 us and two more launches, a whole step with its recomputed forward one and the copies
-// of J 43; as one 20 and 30.  Its bytes (620 a node) take 14 us at the copy rate; a 128 x 64
-// grid, whose bytes take under 1, needs 12: a node's reverse is a chain of some 1500 FP64
-// operations, which two waves per SIMD do not hide.
+// of J 43; as one 20 and 30.  Its bytes (376 read and 216 written a node) take 13 us at the
+// copy rate; a 128 x 64 grid, whose bytes take under 1 and whose 64 workgroups leave most CUs
+// idle, needs 12: the chain of a node's reverse, some 1500 FP64 operations.  On 512 x 256 that
+// chain is hidden behind two waves per SIMD only, all that the grid has (registers allow 3).
 // Away from the interface psi saturates and |grad psi| falls to rounding level; the
 // derivative of the unit normal there has a gain of order lambda / |grad psi| per step
 // and grows without bound, so the normal is differentiated only where

@@ -9,8 +9,8 @@
 //              reductions;
 //   k_node3d   updates every node, its 18 neighbours' pairs read through the caches.
 // g is read twice and the pairs once each way: 432 instead of 336 bytes a node in FP32,
-// 242 instead of 192 in FP16S, 840 instead of 656 in FP64.  Against the march (us a step,
-// 60 x 36 x 54 to 113 x 97 x 301 nodes, periodic):
+// 242 instead of 184 in FP16S, 840 instead of 656 in FP64.  Against the march (us a step,
+// 36 x 60 x 54 to 113 x 97 x 301 nodes, periodic):
 //                      FP64           FP32          FP16S
 //   36 x 60 x 54      66 -> 21       62 -> 16       55 -> 15
 //   46 x 26 x 265     87 -> 47       61 -> 28       56 -> 23
@@ -77,8 +77,10 @@ __global__ void __launch_bounds__(kBlock) k_pairs3d(DevCase<D3Q19, St> c, long n
   if (reduce) write_partials(acc, c.nl, c.part_w, nb, b);
 }
 
-// Waves per SIMD the registers are sized for: 87-91 registers with 4-byte arithmetic, 150 in
-// FP64 (which does not fit 4 waves).  by_xcd: blocks in XCD-aware order; either way the last
+// Waves per SIMD the registers are sized for: 88-100 registers with 4-byte arithmetic and unit
+// rates (105-119 with general ones), 150 in FP64, which does not fit 4 waves.  With walls or
+// general rates FP64 fills the 168 of 3 waves and spills 2-10 (the march's kernel with walls
+// fills 256 and spills 21).  by_xcd: blocks in XCD-aware order; either way the last
 // block goes first, where the pass before ended.  NT: population stores with the
 // non-temporal hint.
 template <class St, bool UNIT, bool VISC, bool WALL, bool NT>

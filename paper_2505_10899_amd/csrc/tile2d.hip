@@ -6,8 +6,8 @@
 // costs that many round trips in a row.  Here a workgroup owns a tile of 2^lx x 2^ly
 // nodes, every lane requests all populations of its node and its share of the halo ring's
 // g at once, phi and psi go to LDS, and after one barrier every lane updates its node: one
-// round trip per step, and with nothing carried from row to row 54 registers in FP32 and
-// 92 in FP64, so that 8 and 5 waves per SIMD hide it.  On the smallest grids, where the
+// round trip per step, and with nothing carried from row to row 50-66 registers in FP32 and
+// 78-96 in FP64, so that 7-8 and 5-6 waves per SIMD hide it.  On the smallest grids, where the
 // chain of a launch (dispatch, pull, stencil, update, store: 5 us) is nearly all of a step,
 // a launch takes three (tile2d_multi).  Measured per step, march against tiles, with the
 // reductions:
