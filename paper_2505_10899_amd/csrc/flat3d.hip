@@ -90,6 +90,7 @@ __global__ void __launch_bounds__(kBlock, (sizeof(typename St::R) == 8 ? 3 : 4))
   using R = typename St::R;
   using IX = unsigned;
   constexpr int Q = L::Q;
+  constexpr bool AHEAD = sizeof(typename St::S) == 2 && !WALL;
   const int last = int(gridDim.x) - 1 - int(blockIdx.x);
   const unsigned n = unsigned(by_xcd ? xcd_tile(last, gridDim.x) : last) * kBlock + threadIdx.x;
   if (long(n) >= c.n) return;
@@ -105,13 +106,7 @@ __global__ void __launch_bounds__(kBlock, (sizeof(typename St::R) == 8 ? 3 : 4))
   for (int d = 0; d < L::D; ++d) J[d] = ldg(c.J + d * c.ns, n);
   // stencils of Eqs. 39-40 over the neighbours' pairs
   const auto* pairs = reinterpret_cast<const Pair<R>*>(c.tmp_phi);
-  R nphi[Q];
-  StencilOut<L, R> st;
-  st.phi = nphi[0] = ldg(pairs, n).x;
-  st.lap = R(0);
-#pragma unroll
-  for (int d = 0; d < 3; ++d) st.gphi[d] = st.gpsi[d] = R(0);
-  static_for<1, Q>([&](auto I) {
+  auto pair_of = [&](auto I) {
     constexpr int i = decltype(I)::value;
     int m = o.s0;
     if constexpr (L::cx[i] > 0) m += o.xp;
@@ -120,7 +115,24 @@ __global__ void __launch_bounds__(kBlock, (sizeof(typename St::R) == 8 ? 3 : 4))
     if constexpr (L::cz[i] < 0) m += o.zm;
     if constexpr (L::cy[i] > 0) m += o.hi ? 0 : o.yp;
     if constexpr (L::cy[i] < 0) m += o.lo ? 0 : o.ym;
-    Pair<R> v = ldg(pairs, unsigned(m));
+    return ldg(pairs, unsigned(m));
+  };
+  Pair<R> pre[AHEAD ? Q : 1];
+  if constexpr (AHEAD) {
+    static_for<1, Q>([&](auto I) { pre[decltype(I)::value] = pair_of(I); });
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  R nphi[Q];
+  StencilOut<L, R> st;
+  st.phi = nphi[0] = ldg(pairs, n).x;
+  st.lap = R(0);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) st.gphi[d] = st.gpsi[d] = R(0);
+  static_for<1, Q>([&](auto I) {
+    constexpr int i = decltype(I)::value;
+    Pair<R> v;
+    if constexpr (AHEAD) v = pre[i];
+    else v = pair_of(I);
     if constexpr (WALL && L::cy[i] != 0) {   // behind a wall: the edge row's wetting ghost
       if (L::cy[i] > 0 ? o.hi : o.lo) {
         v.x = wet_ghost<R>(v.x, L::cy[i] > 0 ? c.np.wet_hi : c.np.wet_lo);
