@@ -481,23 +481,26 @@ bool unit_rates(const vclb_params& p) {
 //    where sections of 96 columns fill the rows (96 x 96 x 150 117 / 126, 96 x 8 x 2000
 //    125 / 131; 192 x 32 x 200, 1.2 million, 114 / 107), but not with general rates (96 x 96 x
 //    200 189 / 161);
-//  - FP16S, whose second reading of g is cheap: periodic from 1.3 million nodes on, where one
-//    section spans the rows and is its own halo (96 x 96 x 200 110 / 121, 96 x 8 x 2000 76 / 91,
-//    32 x 64 x 1000 119 / 126) or the grid has only 8 or 16 rows (64 x 16 x 1500 78 / 89), else
-//    two passes (64 x 64 x 350 76 / 75, 128 x 128 x 400 351 / 356, 256 x 256 x 100 457 / 356;
-//    with walls 96 x 96 x 384 221 / 195).
+//  - FP16S, whose second reading of g is cheap: two passes (96 x 96 x 384 198 / 190, 128 x 128
+//    x 200 191 / 174, 256 x 256 x 100 458 / 331, with walls 96 x 96 x 384 219 / 195), but for
+//    periodic grids with unit rates (general ones 32 x 64 x 1000 131 / 119) whose 180 bytes a
+//    node with the pairs exceed the 256 MB last-level cache: there the march, if the 172
+//    without them fit (64 x 64 x 378 75 / 85, 96 x 96 x 168 75 / 84, 192 x 24 x 336 77 / 82;
+//    smaller: 96 x 96 x 156 74 / 66, larger: 96 x 96 x 173 89 / 88), and on rows of 32, whose
+//    one section is its own halo, at any size (32 x 64 x 1172 135 / 141).
 bool flat3d_chosen(const vclb_params& p) {
   const long n = long(p.nx) * p.ny * p.nz;
   if (!two_passes_ok(p)) return false;
-  constexpr long kMiddle = 5L << 18;
   if (p.storage == VCLB_FP16S) {
-    const bool spans = (p.nx == 96 || p.nx == 32) && p.ny % 8 == 0;
-    const bool few_rows = p.nx % 32 == 0 && p.nx < 96 && (p.ny == 8 || p.ny == 16);
-    return wall_y(p) || n < kMiddle || !(spans || few_rows);
+    constexpr size_t kCache = size_t(256) << 20;
+    const size_t march = size_t(n) * 172, passes = size_t(n) * 180;
+    const bool sections = p.ny >= 8 && p.nx <= 256 && (p.nx % 64 == 0 || p.nx % 96 == 0);
+    const bool marches = (p.nx == 32 && p.ny >= 8) || (sections && march <= kCache);
+    return !(marches && passes > kCache && !wall_y(p) && unit_rates(p));
   }
   if (size_t(p.nx) * storage_bytes(p.storage) % 128 != 0) return true;
   if (p.storage == VCLB_FP64) return !(n >= (1L << 21) || (n >= (1L << 20) && p.nx % 32 == 0));
-  return !(n >= (1L << 21) || (n >= kMiddle && p.nx % 96 == 0 && unit_rates(p)));
+  return !(n >= (1L << 21) || (n >= (5L << 18) && p.nx % 96 == 0 && unit_rates(p)));
 }
 
 vclb::Tile default_tile(const vclb_params& p, int ncu, bool wide_ok = true, bool multi = true) {

@@ -32,10 +32,12 @@ GENERAL = dict(s_g=(0.0, 1.3, 1.2) + (0.0,) * 16)
     ("fp32", (96, 96, 200), "march", {}), ("fp32", (96, 8, 2000), "march", {}), ("fp32", (96, 96, 384), "march", {}),
     ("fp32", (96, 96, 200), "two_passes", GENERAL), ("fp32", (192, 32, 200), "two_passes", {}),
     ("fp32", (64, 64, 350), "two_passes", {}), ("fp32", (90, 90, 400), "two_passes", {}),
-    ("fp16s", (96, 96, 200), "march", {}), ("fp16s", (96, 8, 2000), "march", {}), ("fp16s", (64, 16, 1500), "march", {}),
-    ("fp16s", (64, 8, 3000), "march", GENERAL), ("fp16s", (32, 64, 1000), "march", {}),
-    ("fp16s", (96, 96, 200), "two_passes", dict(wall_y=True)), ("fp16s", (96, 96, 100), "two_passes", {}),
-    ("fp16s", (64, 64, 350), "two_passes", {}), ("fp16s", (256, 256, 100), "two_passes", {}),
+    ("fp16s", (64, 64, 378), "march", {}), ("fp16s", (96, 8, 2000), "march", {}), ("fp16s", (64, 16, 1500), "march", {}),
+    ("fp16s", (32, 64, 1000), "march", {}), ("fp16s", (32, 8, 15625), "march", {}),
+    ("fp16s", (64, 64, 378), "two_passes", dict(wall_y=True)), ("fp16s", (32, 64, 1000), "two_passes", GENERAL),
+    ("fp16s", (64, 64, 352), "two_passes", {}), ("fp16s", (64, 64, 396), "two_passes", {}),
+    ("fp16s", (72, 72, 299), "two_passes", {}), ("fp16s", (320, 16, 303), "two_passes", {}),
+    ("fp16s", (96, 96, 384), "two_passes", {}), ("fp16s", (256, 256, 100), "two_passes", {}),
     ("fp16s", (32, 8, 3000), "two_passes", {})])
 def test_d3q19(storage, size, form, change):
     nx, ny, nz = size
