@@ -231,8 +231,7 @@ int vclb_case_get_tile(const vclb_case* c, int32_t* bx, int32_t* ty, int32_t* by
    other lattice's, lane tiles beyond 2^26 nodes or with more tiles than the workspace holds
    partial sums for, three steps per launch beyond 2^16 nodes, for a case of a batch or with
    the global volume correction (16 x 16 also for coupled FP64), two passes from 2^28 nodes on.
-   The state does not depend on the form, bit for bit; but D3Q19 in FP32 the march and the two
-   passes agree to rounding. */
+   The state does not depend on the form, bit for bit. */
 #define VCLB_FORM_MARCH      0
 #define VCLB_FORM_LANE_TILES 1
 #define VCLB_FORM_TWO_PASSES 2

@@ -90,7 +90,15 @@ __global__ void __launch_bounds__(kBlock, (sizeof(typename St::R) == 8 ? 3 : 4))
   using R = typename St::R;
   using IX = unsigned;
   constexpr int Q = L::Q;
-  constexpr bool AHEAD = sizeof(typename St::S) == 2 && !WALL;
+  // APART: sums as the march's compiled form has them in FP32, whose one kernel tests for walls:
+  // grad phi with each product made once, fused into the first component that takes it, and g's
+  // inverse transform with its products rounded (bit for bit the march's results).
+  constexpr bool APART = sizeof(typename St::S) == 4;
+  // AHEAD: the pairs are requested before the sums over them, like the populations.  Without,
+  // the compiler waits for them one after the other where the sums are spelled out (FP16S
+  // periodic, 128 x 128 x 200: 187 -> 172 us, with general rates 206 -> 173) or walls stand
+  // between them (FP32, 61 x 45 x 130: 34.3 -> 31.8).
+  constexpr bool AHEAD = sizeof(typename St::S) == (WALL ? 4 : 2);
   const int last = int(gridDim.x) - 1 - int(blockIdx.x);
   const unsigned n = unsigned(by_xcd ? xcd_tile(last, gridDim.x) : last) * kBlock + threadIdx.x;
   if (long(n) >= c.n) return;
@@ -140,20 +148,33 @@ __global__ void __launch_bounds__(kBlock, (sizeof(typename St::R) == 8 ? 3 : 4))
       }
     }
     nphi[i] = v.x;
-    st.lap += R(6.0 * L::w[i]) * (v.x - st.phi);
     constexpr int cc[3] = {L::cx[i], L::cy[i], L::cz[i]};
+    if constexpr (APART) {
+      st.lap = fma_of(R(6.0 * L::w[i]), v.x - st.phi, st.lap);
+      constexpr int lead = cc[0] != 0 ? 0 : cc[1] != 0 ? 1 : 2;
 #pragma unroll
-    for (int d = 0; d < 3; ++d)
-      if (cc[d] != 0) {
-        st.gphi[d] += R(3.0 * L::w[i] * cc[d]) * v.x;
-        st.gpsi[d] += R(3.0 * L::w[i] * cc[d]) * v.y;
-      }
+      for (int d = 0; d < 3; ++d)
+        if (cc[d] != 0) {
+          const R a = R(3.0 * L::w[i] * cc[d]);
+          st.gphi[d] = d == lead ? fma_of(a, v.x, st.gphi[d]) : st.gphi[d] + rounded(a * v.x);
+          st.gpsi[d] = fma_of(a, v.y, st.gpsi[d]);
+        }
+    } else {
+      st.lap += R(6.0 * L::w[i]) * (v.x - st.phi);
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+        if (cc[d] != 0) {
+          st.gphi[d] += R(3.0 * L::w[i] * cc[d]) * v.x;
+          st.gpsi[d] += R(3.0 * L::w[i] * cc[d]) * v.y;
+        }
+    }
   });
   (void)phi_of_pulled<L, St>(g, ps, c.np.rest);
   NodeOut<L, R> out;
-  node_update_mom_s<L, R, true, St::shifted, UNIT, VISC, true>(c.np, st, g, f, J, out);
-  // with walls the march converts f behind the wall terms' branches, formed before them
-  if constexpr (WALL && sizeof(typename St::S) == 2) {
+  node_update_mom_s<L, R, true, St::shifted, UNIT, VISC, true, APART>(c.np, st, g, f, J, out);
+  // with walls the march adds the wall terms to f, and converts it, in other blocks than those
+  // that form it
+  if constexpr (WALL && sizeof(R) == 4) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) f[i] = formed(f[i]);
   }

@@ -537,13 +537,15 @@ __device__ __forceinline__ void to_moments(const R (&v)[L::Q], R (&m)[L::Q]) {
 }
 
 // v = M^{-1} m = M^T diag(1 / |M_k|^2) m (m is scaled in place): for each pair the even
-// rows give the common part and the odd rows the antisymmetric part
-template <class L, class R>
+// rows give the common part and the odd rows the antisymmetric part.  APART: see
+// node_update_mom_s.
+template <class L, class R, bool APART = false>
 __device__ __forceinline__ void from_moments(R (&m)[L::Q], R (&v)[L::Q]) {
   R (&a)[L::Q] = m;
   static_for<0, L::Q>([&](auto K) {
     constexpr int k = decltype(K)::value;
     a[k] = m[k] * R(1.0 / double(row_norm<L>(k)));
+    if constexpr (APART) a[k] = rounded(a[k]);
   });
   static_for<0, L::Q>([&](auto I) {
     constexpr int i = decltype(I)::value;
@@ -607,7 +609,10 @@ struct StencilOut {
 // VISC: the stress rows relax at the node's own rate (stress_rate).
 // MARCH: sums of two products whose fused one the compiler is free to choose are spelled out
 // as the section march's compiled form has them, see node_update_d2q9.
-template <class L, class R, bool COUPLED, bool SH, bool UNIT = false, bool VISC = false, bool MARCH = false>
+// APART: the products of g's inverse transform are rounded before they are summed, as in the
+// march's kernel with wall tests, which sinks g's sums into other blocks than their products.
+template <class L, class R, bool COUPLED, bool SH, bool UNIT = false, bool VISC = false, bool MARCH = false,
+          bool APART = false>
 __device__ __forceinline__ void node_update_mom_s(const NodeParams<L, R>& p, const StencilOut<L, R>& st,
                                                   R (&g)[L::Q], R (&f)[L::Q], R (&J)[L::D], NodeOut<L, R>& out) {
   constexpr int Q = L::Q, D = L::D;
@@ -692,7 +697,7 @@ __device__ __forceinline__ void node_update_mom_s(const NodeParams<L, R>& p, con
         }
       }
     });
-    from_moments<L, R>(m, g);
+    from_moments<L, R, APART>(m, g);
   }
   // f (Eq. 25) in moment space
   if constexpr (COUPLED) {

@@ -70,10 +70,9 @@ def test_lane_tiles_equal_the_march_vortex(nx, ny, storage):
 
 @pytest.mark.parametrize("wall,visc,general", [(False, 1.0, False), (True, 3.75, False), (True, 1.0, True),
                                                (False, 3.75, True)])
-@pytest.mark.parametrize("nx,ny,nz", [(36, 30, 40), (61, 45, 130), (64, 16, 24)])
-@pytest.mark.parametrize("storage", ["fp64", "fp16s"])
+@pytest.mark.parametrize("nx,ny,nz", [(36, 30, 40), (61, 45, 130), (64, 16, 24), (96, 80, 250)])
+@pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s"])
 def test_two_passes_equal_the_march(nx, ny, nz, storage, wall, visc, general):
-    """(In FP32 the two forms agree to rounding only: see test_gpu_flat3d.py.)"""
     print("case:", nx, ny, nz, storage, wall, visc, general, flush=True)
     c1 = (0.47 * nx + 0.13, 0.52 * ny + 0.21, 0.0)
     p = W.CaseParams(lattice="D3Q19", nx=nx, ny=ny, nz=nz, storage=storage, sigma=0.005, nu=0.05, rho_light=0.1,
@@ -89,7 +88,13 @@ def test_two_passes_equal_the_march(nx, ny, nz, storage, wall, visc, general):
     R = min(nx, ny) / 5.0 * (1.0 + 0.1 * np.cos(2 * np.pi * z / nz))
     phi0 = 0.5 + 0.5 * np.tanh(2.0 * (R - np.hypot(x - c1[0], y - c1[1])) / p.W)
     u0 = 0.02 * np.stack([np.sin(2 * np.pi * y / ny), np.zeros(x.shape), np.cos(2 * np.pi * x / nx)])
-    _same(_states(p, phi0, u0, 6), _states(p, phi0, u0, 6, tile=(32, 8, 8)))
+    ref = _states(p, phi0, u0, 6)
+    _same(ref, _states(p, phi0, u0, 6, tile=(32, 8, 8)))
+    if storage != "fp64":
+        _same(ref, _states(p, phi0, u0, 6, tile=(96, 8, 8)))   # 768 lanes
+    if general:
+        c2 = (0.8 * nx, 0.25 * ny, 0.0)                          # two labels
+        _same(ref, _states(p.replace(label_centres=[c1, c2]), phi0, u0, 6, tile=(32, 8, 8)))
 
 
 @pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16s"])
