@@ -247,11 +247,9 @@ int vclb_case_set_form(vclb_case* c, int32_t form, int32_t w, int32_t h);
    {8, ..., 128}, and, for a case that steps in tiles of one lane per node by default, the
    tile shapes of its size (those of three steps a launch by whole launches: `steps` is then
    rounded up to a multiple of three).  D3Q19: the two passes, where they are the default, and
-   six column sections with their planes cut to fill 1..4 workgroups per CU, and (4-byte
-   storage) three 768-lane sections at one per CU; in FP32, where the two passes and the
-   sections agree to rounding only, just the two passes where they are the default.  The
-   choice does not change a case's results.  Synchronises the stream; VCLB_ESTATE before
-   init. */
+   six column sections with their planes cut to fill 1..4 workgroups per CU, and (4- and 2-byte
+   storage) three 768-lane sections at one per CU.  The choice does not change a case's
+   results.  Synchronises the stream; VCLB_ESTATE before init. */
 int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void* stream);
 
 /* Initial state from phi0 (N doubles) and u0 (D*N doubles, NULL for u = 0; ignored in

@@ -1046,17 +1046,13 @@ int vclb_case_autotune(vclb_case* c, const char* cache_path, int32_t steps, void
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       ncu = 256;
     const int shapes[][2] = {{32, 8}, {64, 4}, {16, 16}, {32, 4}, {64, 2}, {16, 8}, {96, 8}, {48, 16}, {64, 12}};
-    // the two passes where they are the default; in FP32, where a march's results differ from
-    // theirs by rounding, alone: tuning changes no results
-    const bool passes = default_tile(p, 256).flat;
-    if (passes) {
+    if (default_tile(p, 256).flat) {   // the two passes where they are the default
       vclb::Tile t = c->tile;
       t.flat = true;
       cands.push_back(t);
     }
     for (const auto& sh : shapes)
       for (int per_cu : {1, 2, 3, 4}) {
-        if (passes && p.storage == VCLB_FP32) continue;
         if (sh[0] * sh[1] > 256 && (p.storage == VCLB_FP64 || per_cu > 1)) continue;   // wide: one per CU
         const long cols = long((p.nx + sh[0] - 1) / sh[0]) * ((p.ny + sh[1] - 1) / sh[1]);
         const long segs = std::max(1L, per_cu * long(ncu) / cols);

@@ -120,7 +120,7 @@ def test_no_candidate_changes_results(tmp_path, storage, nz):
     ref = ref.get_state()
     timed = [k for k in entry["candidates"] if k[-1] > 0]
     # 2D: lane tiles (16 x 16 not in coupled FP64) and 5 heights of 3 or 5 widths of march
-    assert len(timed) >= ((4 + 15 if storage == "fp64" else 5 + 25) if nz == 1 else (1 if storage == "fp32" else 10))
+    assert len(timed) >= ((4 + 15 if storage == "fp64" else 5 + 25) if nz == 1 else 10)
     for bx, ty, by3, lx, ly, flat, _ in timed:
         print("case:", storage, nz, (bx, ty, by3, lx, ly, flat), flush=True)
         new = dict(entry, bx=bx, ty=ty, by3=by3, lane_tile=[lx, ly], flat=flat)
