@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(kBlock) k_pairs3d(DevCase<D3Q19, St> c, long n
 }
 
 // Waves per SIMD the registers are sized for: 88-100 registers with 4-byte arithmetic and unit
-// rates (105-119 with general ones), 150 in FP64, which does not fit 4 waves.  With walls or
+// rates (109-119 with general ones), 150 in FP64, which does not fit 4 waves.  With walls or
 // general rates FP64 fills the 168 of 3 waves and spills 2-10 (the march's kernel with walls
 // fills 256 and spills 21).  by_xcd: blocks in XCD-aware order; either way the last
 // block goes first, where the pass before ended.  NT: population stores with the
